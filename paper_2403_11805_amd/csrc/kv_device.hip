@@ -417,7 +417,7 @@ static int score_geom(const kv_shape_t* shape, int32_t n_queries, int32_t n_vali
     g.RB = (n_queries + 31) / 32;
     g.rows_p = g.RB * 32;
     g.n_rb = (s.n_q_heads / s.n_kv_heads) * g.RB;
-    *nrbw = g.n_rb == 1 ? 1 : 2;
+    *nrbw = g.n_rb == 1 ? 1 : (g.n_rb == 2 ? 2 : shared_blocks_per_wave(s.head_dim));
     g.n_rg = (g.n_rb + *nrbw - 1) / *nrbw;
     g.rg_per_wg = std::min(g.n_rg, 4);
     // several row groups per kv head: the workgroup shares each K tile through LDS and all
@@ -435,6 +435,29 @@ static int score_geom(const kv_shape_t* shape, int32_t n_queries, int32_t n_vali
     return KV_OK;
 }
 
+// A run is what one wavefront (one workgroup where K is shared through LDS) walks alone, so few heads over a
+// short context leave most of the chip idle with the longest runs: they are halved until the launch has some
+// 256 workgroups where K is shared, 128 where a workgroup holds four runs side by side - but not below four
+// (two) tiles, since a run opens with two trips to memory (query rows, first tile) before it has anything to
+// do.  Measured (us per call, longest runs / 128 / 256 / 512 workgroups wanted):
+//   18 layers, 8 heads on one kv head of 256, 4096 tokens, R 32     49.9 / 36.6 / 33.3 / 33.8
+//   4 layers, 16 heads on 4 kv heads of 128, 8192 tokens, R 64      55.0 / 37.8 / 29.1 / 31.6
+//   28 layers, 28 heads on 4 kv heads of 128, 4096 tokens, R 64     104.9 / 105.0 / 105.2 / 114.7
+//   18 layers, one head of 256, 4096 tokens, R 32 (four runs side by side)   28.0 / 20.8 / 23.7 / 23.7
+//   6 layers, 12 heads of 256, 2048 tokens, R 32 (likewise)                  28.5 / 28.5 / 32.4 / 29.7
+static void shorten_runs(ScoreGeom* g) {
+    const bool shared = g->tile_par == 1;
+    const int64_t heads = static_cast<int64_t>(g->L) * g->Hkv * ((g->n_rg + g->rg_per_wg - 1) / g->rg_per_wg);
+    const int64_t wanted = shared ? 256 : 128;
+    const int min_run = shared ? 4 : 2;
+    int run = shared ? 64 : 8;
+    auto groups = [&] { return ((g->n_tiles + run - 1) / run + g->tile_par - 1) / g->tile_par * heads; };
+    while (run > min_run && groups() < wanted) run /= 2;
+    if (run >= g->n_tiles) return;
+    g->run_len = run;
+    g->n_runs = (g->n_tiles + run - 1) / run;
+}
+
 static uint64_t ws_floats_tile(const ScoreGeom& g) {
     return static_cast<uint64_t>(g.L) * g.Hq * g.n_tiles * g.rows_p;
 }
@@ -445,20 +468,9 @@ static uint64_t ws_floats_run(const ScoreGeom& g) {
     return static_cast<uint64_t>(g.L) * g.Hq * g.n_runs * g.rows_p;
 }
 
-uint64_t kv_score_workspace_bytes(const kv_shape_t* shape, int32_t n_queries) {
-    ScoreGeom g;
-    int nrbw;
-    if (!shape || score_geom(shape, n_queries, shape->n_tokens, KV_NORM_VISIBLE, &g, &nrbw) != KV_OK) return 0;
+static uint64_t score_ws_bytes(const ScoreGeom& g) {
     const uint64_t bytes = (ws_floats_tile(g) + ws_floats_sub(g) + 3 * ws_floats_run(g)) * sizeof(float);
     return (bytes + 255) & ~static_cast<uint64_t>(255);
-}
-
-int32_t kv_score_chunks(const kv_shape_t* shape, const void* q, int32_t n_queries, const void* kv,
-                        int32_t norm_mode, void* workspace, uint64_t workspace_bytes,
-                        float* chunk_mass, float* density, void* stream) {
-    if (!shape) return fail(KV_EINVAL, "NULL shape");
-    return kv_score_chunks_valid(shape, q, n_queries, kv, shape->n_tokens, norm_mode, workspace, workspace_bytes,
-                                 chunk_mass, density, stream);
 }
 
 // LDS of score_head_kernel for this geometry (one workgroup scores a whole head and keeps the
@@ -468,6 +480,31 @@ static uint64_t score_head_lds_bytes(const ScoreGeom& g, int head_dim) {
     const uint64_t head_lds = (static_cast<uint64_t>(g.N / g.sb_tokens) * 32 + 2ull * g.n_runs * 32 + 4 * 5 * 32 + 64) *
                               sizeof(float);
     return (g.n_rb == 1 && g.L * g.Hkv >= 256 && head_lds <= 40960 && head_dim <= 128) ? head_lds : 0;
+}
+
+// The geometry to launch with, given `available` bytes of scratch.  Shorter runs need a little more (three floats
+// per row and run); a workspace that holds the longest runs only - one made for another shape, or the static
+// array - is served with these, as long as it holds them.
+static ScoreGeom fitted_runs(const ScoreGeom& g, int head_dim, uint64_t available) {
+    if (score_head_lds_bytes(g, head_dim)) return g;
+    ScoreGeom s = g;
+    shorten_runs(&s);
+    return score_ws_bytes(s) <= available ? s : g;
+}
+
+uint64_t kv_score_workspace_bytes(const kv_shape_t* shape, int32_t n_queries) {
+    ScoreGeom g;
+    int nrbw;
+    if (!shape || score_geom(shape, n_queries, shape->n_tokens, KV_NORM_VISIBLE, &g, &nrbw) != KV_OK) return 0;
+    return std::max(score_ws_bytes(g), score_ws_bytes(fitted_runs(g, shape->head_dim, ~0ull)));
+}
+
+int32_t kv_score_chunks(const kv_shape_t* shape, const void* q, int32_t n_queries, const void* kv,
+                        int32_t norm_mode, void* workspace, uint64_t workspace_bytes,
+                        float* chunk_mass, float* density, void* stream) {
+    if (!shape) return fail(KV_EINVAL, "NULL shape");
+    return kv_score_chunks_valid(shape, q, n_queries, kv, shape->n_tokens, norm_mode, workspace, workspace_bytes,
+                                 chunk_mass, density, stream);
 }
 
 static int32_t score_launch(const kv_shape_t* shape, const ScoreGeom& g, int nrbw, const void* q, const void* kv,
@@ -483,11 +520,12 @@ int32_t kv_score_chunks_valid(const kv_shape_t* shape, const void* q, int32_t n_
     if (!q || !kv || !workspace || !chunk_mass || !density) return fail(KV_EINVAL, "NULL device pointer");
     if (!aligned(q, 16) || !aligned(kv, 16) || !aligned(workspace, 256))
         return fail(KV_EINVAL, "q/kv must be 16-byte aligned, workspace 256-byte aligned");
-    const uint64_t need = kv_score_workspace_bytes(shape, n_queries);
+    const uint64_t need = score_ws_bytes(g);
     if (workspace_bytes < need)
         return fail(KV_ENOMEM, "workspace %llu bytes, %llu needed",
                     static_cast<unsigned long long>(workspace_bytes), static_cast<unsigned long long>(need));
-    return score_launch(shape, g, nrbw, q, kv, workspace, chunk_mass, density, stream);
+    return score_launch(shape, fitted_runs(g, shape->head_dim, workspace_bytes), nrbw, q, kv, workspace, chunk_mass,
+                        density, stream);
 }
 
 // ---- scoring for callers that cannot allocate: the partials live in a static device array ----
@@ -526,7 +564,7 @@ int32_t kv_score_chunks_static(const kv_shape_t* shape, const void* q, int32_t n
     if (!q || !kv || !chunk_mass || !density) return fail(KV_EINVAL, "NULL device pointer");
     if (!aligned(q, 16) || !aligned(kv, 16)) return fail(KV_EINVAL, "q/kv must be 16-byte aligned");
     // a head scored by one workgroup keeps its partials in LDS and needs no scratch at all
-    const uint64_t need = score_head_lds_bytes(g, shape->head_dim) ? 0 : kv_score_workspace_bytes(shape, n_queries);
+    const uint64_t need = score_head_lds_bytes(g, shape->head_dim) ? 0 : score_ws_bytes(g);
     if (need > kStaticScratchBytes)
         return fail(KV_ENOMEM, "scoring this shape needs %llu bytes of scratch, the static buffer holds %llu: "
                     "use kv_score_chunks with a workspace",
@@ -534,7 +572,8 @@ int32_t kv_score_chunks_static(const kv_shape_t* shape, const void* q, int32_t n
     void* ws = nullptr;
     if (int rc = static_scratch(&ws)) return rc;
     // every slot of the partial planes is written before it is read: nothing has to start at zero
-    return score_launch(shape, g, nrbw, q, kv, ws, chunk_mass, density, stream);
+    return score_launch(shape, fitted_runs(g, shape->head_dim, kStaticScratchBytes), nrbw, q, kv, ws, chunk_mass,
+                        density, stream);
 }
 
 static int32_t score_launch(const kv_shape_t* shape, const ScoreGeom& g, int nrbw, const void* q, const void* kv,

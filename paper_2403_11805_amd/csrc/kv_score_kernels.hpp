@@ -344,7 +344,7 @@ __device__ __forceinline__ void fast_epilogue(const v16f_t& acc, float scale_log
 }
 
 // Variant for grouped-query attention: the 2-4 wavefronts of a workgroup hold
-// the row blocks (two each) of different query heads that read the SAME kv head,
+// the row blocks (shared_blocks_per_wave each) of different query heads that read the SAME kv head,
 // so K is fetched once per workgroup (fully coalesced, 16 bytes per thread and
 // access), staged in LDS (two buffers of two tiles; the 16-byte pieces of a row
 // are permuted by its row number so that the operand reads are bank-conflict
@@ -361,11 +361,17 @@ __device__ __forceinline__ void fast_epilogue(const v16f_t& acc, float scale_log
 //  - the general pass over the whole fast range again if some sum left the safe
 //    range there (workgroup-wide decision), or instead of the fast pass if a
 //    wavefront holds only one row block.
+//
+// Row blocks per wavefront: two, but one at head_dim 256, where the two query blocks alone would hold 128
+// registers: 171 spilled, and 4.4 us went by per tile of 32 tokens (18 layers x 8 heads x 4096 tokens, the same
+// run lengths: 82.2 -> 33.3 us per call; one wavefront per SIMD with 512 registers instead: 45.2 us).
+constexpr int shared_blocks_per_wave(int head_dim) { return head_dim == 256 ? 1 : 2; }
+
 template <int D, int SBT>
 __global__ __launch_bounds__(256, 2) void score_tiles_shared_kernel(const _Float16* __restrict__ q,
                                                                     const _Float16* __restrict__ kv,
                                                                     ScoreGeom g, ScoreWs ws) {
-    constexpr int NRBW = 2;
+    constexpr int NRBW = shared_blocks_per_wave(D);
     constexpr int KS = D / 16;
     constexpr int kRowPieces = D / 8;               // 16-byte pieces per token row
     constexpr int kTilePieces = 32 * kRowPieces;
@@ -390,7 +396,7 @@ __global__ __launch_bounds__(256, 2) void score_tiles_shared_kernel(const _Float
     const int qh_per_kv = g.Hq / g.Hkv;
     // tiles from here on touch the causal diagonal
     const int first_tail_tile = (g.Nv - g.R + 1) / 32;
-    const bool two_blocks = rg * NRBW + 1 < g.n_rb;
+    const bool two_blocks = NRBW == 2 && rg * NRBW + 1 < g.n_rb;
     // the fast pass needs both row blocks in every wavefront (workgroup-uniform)
     const int fast_end = (g.n_rb % NRBW == 0) ? min(tile_end, max(first_tail_tile, tile_begin)) : tile_begin;
 
@@ -456,6 +462,17 @@ __global__ __launch_bounds__(256, 2) void score_tiles_shared_kernel(const _Float
                 a[u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kreg[ks], qreg[u][ks], a[u], 0, 0, 0);
     };
 
+    // What tile_epilogue stores for a tile that no row sees.
+    auto padding_tile = [&](int tile) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < NRBW; ++u) {
+            if (half != 0 || row[u] < 0) continue;
+            ws.m_tile[(static_cast<int64_t>(lh[u]) * g.n_tiles + tile) * g.rows_p + row[u]] = -INFINITY;
+#pragma unroll
+            for (int k = 0; k < SBT; ++k)
+                ws.e_sub[(static_cast<int64_t>(lh[u]) * g.n_tiles * SBT + tile * SBT + k) * g.rows_p + row[u]] = 0.0f;
+        }
+    };
     // General pass over tiles [from, to): plain double buffering, partials right behind the MFMAs.
     auto general_pass = [&](int from, int to) __attribute__((always_inline)) {
         su4_t st[kPerThread];
@@ -468,6 +485,10 @@ __global__ __launch_bounds__(256, 2) void score_tiles_shared_kernel(const _Float
             if (more) fetch(st, t + TS, to);
             if (active) {
                 for (int j = 0; j < TS && t + j < to; ++j) {
+                    if ((t + j) * 32 >= g.Nv) {         // padding only: no row sees it
+                        padding_tile(t + j);
+                        continue;
+                    }
                     v16f_t a[NRBW];
                     logits(a, buf, j);
 #pragma unroll
@@ -519,7 +540,7 @@ __global__ __launch_bounds__(256, 2) void score_tiles_shared_kernel(const _Float
 #pragma unroll
             for (int i = 0; i < KS * NRBW; ++i) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x402, (2 * (66 + 2 * SBT)) / (KS * NRBW) + 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x402, (66 + 2 * SBT) / KS + 1, 0);
             }
         };
         // stage s (TS tiles from t) is in kstage[s & 1]; `next` holds stage s + 1, `far` receives

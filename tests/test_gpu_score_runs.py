@@ -1,0 +1,82 @@
+"""GPU parity of scoring where the launch shortens its runs of tiles (few heads over a short context) and where a
+wavefront of the shared-K kernel holds a single row block (head_dim 256), against the fp64 oracle.
+
+Bar: 1e-4 relative, as everywhere for chunk masses and densities (fp32 sums of fp32 exponentials)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2403_11805_amd as kvs
+from paper_2403_11805_amd import synth
+
+from gpu_util import DEV, both_shapes, gpu_score
+
+pytestmark = pytest.mark.gpu
+
+
+def score_with(ks, q, kv, n_valid, ws_bytes):
+    cm = torch.full((ks.n_layers, ks.n_q_heads, ks.n_chunks), float("nan"), dtype=torch.float32, device=DEV)
+    d = torch.full((ks.n_chunks,), float("nan"), dtype=torch.float32, device=DEV)
+    ws = torch.full((ws_bytes,), 0xff, dtype=torch.uint8, device=DEV)
+    kvs.kv_score_chunks_valid(ks, q.to(DEV), kv.to(DEV), n_valid, oracle.NORM_VISIBLE, ws, cm, d)
+    torch.cuda.synchronize()
+    return cm.cpu().numpy(), d.cpu().numpy()
+
+
+def check(got, want):
+    for g, w in zip(got, want):
+        assert np.all(np.isfinite(g))
+        np.testing.assert_allclose(g, w, rtol=1e-4, atol=1e-30)
+
+
+@pytest.mark.parametrize("geom,R,n_valid", [
+    ((1, 1, 3, 256, 1056, 16, 64), 32, 1056),    # head_dim 256, three row blocks: one wavefront of four without work
+    ((2, 1, 8, 256, 544, 8, 64), 23, 471),       # eight blocks in two workgroups, 17 tiles, the last two padding only
+    ((1, 1, 2, 256, 256, 32, 256), 33, 97),      # two heads of two blocks; most of the cache is padding
+    ((1, 1, 4, 128, 160, 32, 64), 5, 160),       # 5 tiles: a run of four and one of one
+    ((1, 1, 4, 64, 128, 16, 64), 32, 128),       # 4 tiles: nothing to shorten
+    ((3, 1, 1, 64, 96, 16, 64), 9, 70),          # four runs side by side, 3 tiles: runs of two and one, padding behind
+    ((200, 1, 4, 64, 256, 16, 64), 32, 250),     # enough heads: two runs of four tiles
+])
+def test_short_runs(geom, R, n_valid):
+    ks, os_ = both_shapes(synth.Geometry(*geom))
+    kv = synth.make_kv(synth.Geometry(*geom), 61, "cpu", 1, 4.0)
+    q = (synth.make_q(synth.Geometry(*geom), 61, R).float() * 6).to(torch.float16)
+    want = oracle.score_chunks_valid(os_, q.numpy(), kv.numpy(), n_valid, oracle.NORM_VISIBLE)
+    kv[:, :, :, n_valid:] = float("nan")
+    check(score_with(ks, q, kv, n_valid, kvs.kv_score_workspace_bytes(ks, R)), want)
+
+
+@pytest.mark.parametrize("D,hot_token", [(256, 3), (256, 140), (256, 900), (128, 140)])
+def test_huge_logit_in_a_short_run(D, hot_token):
+    """A key far above the row references of its run: the run is redone through the general pass."""
+    g = synth.Geometry(1, 1, 4, D, 1024, 16, 64)
+    ks, os_ = both_shapes(g)
+    kv = (synth.make_kv(g, 29, "cpu").float() * 0.05).to(torch.float16)
+    kv[0, 0, 0, hot_token] = 20.0
+    q = torch.full((1, 4, 32, D), 2.0, dtype=torch.float16)
+    check(gpu_score(ks, q.to(DEV), kv.to(DEV), oracle.NORM_NONE),
+          oracle.score_chunks(os_, q.numpy(), kv.numpy(), oracle.NORM_NONE))
+
+
+@pytest.mark.parametrize("geom,R,longest", [
+    ((1, 1, 4, 128, 2048, 16, 64), 32, 64),
+    ((1, 1, 1, 64, 2048, 16, 64), 32, 8),
+])
+def test_workspace_that_holds_the_longest_runs_only(geom, R, longest):
+    """A workspace without room for the run planes of shorter runs is served with the longest ones; one byte less
+    than these need is refused."""
+    g = synth.Geometry(*geom)
+    ks, os_ = both_shapes(g)
+    rows, tiles = (R + 31) // 32 * 32, g.N // 32
+    runs = (tiles + longest - 1) // longest
+    least = 4 * g.L * g.Hq * rows * (tiles + g.N // min(g.T, 32) + 3 * runs)
+    least = (least + 255) // 256 * 256
+    assert least < kvs.kv_score_workspace_bytes(ks, R)
+    kv = synth.make_kv(g, 67, "cpu", 1, 4.0)
+    q = (synth.make_q(g, 67, R).float() * 6).to(torch.float16)
+    check(score_with(ks, q, kv, g.N, least), oracle.score_chunks(os_, q.numpy(), kv.numpy(), oracle.NORM_VISIBLE))
+    with pytest.raises(kvs.KvError) as err:
+        score_with(ks, q, kv, g.N, least - 1)
+    assert err.value.code == kvs.KV_ENOMEM
