@@ -488,14 +488,14 @@ typedef struct {
 
 /* Handle of the recompute path.  The projections of up to KV_RECOMPUTE_OWN_GEMM_ROWS recomputed
  * tokens (what a plan of Eq. 4 recomputes beside a Load) run on the library's own MFMA GEMM,
- * which is the faster one there (0.26 against 0.34 ms per Llama-2-7B layer at 128 tokens, 0.33
- * against 0.35 at 256, 0.46 against 0.49 at 512, rocBLAS with its best kernels); larger ones are handed
+ * which is the faster one there (per Llama-2-7B layer 0.19 ms at 128 tokens, 0.28 at 304, 0.37 at 512;
+ * at 1024 0.635 against 0.644 ms with rocBLAS); larger ones are handed
  * to rocBLAS, which is loaded on creation if it is installed (the handle then owns that
  * library's handle, whose device workspace lives until kv_recompute_destroy).  Without
  * rocBLAS, or with KVSWITCH_OWN_GEMM=1 in the environment at creation, every size runs on the
- * library's own kernel (about half the GEMM library's rate at thousands of rows).  NULL on
+ * library's own kernel (1.1 PFLOP/s at 4096 rows).  NULL on
  * failure (kv_last_error has the text).  One handle serves one stream at a time. */
-#define KV_RECOMPUTE_OWN_GEMM_ROWS 512
+#define KV_RECOMPUTE_OWN_GEMM_ROWS 1024
 typedef struct kv_recompute kv_recompute_t;
 kv_recompute_t* kv_recompute_create(void);
 void            kv_recompute_destroy(kv_recompute_t* rc);

@@ -1,7 +1,7 @@
 // libkvswitch: recompute of interleaved chunks through one Llama-style block
 // (Sec. 3.3, "Making interleaved chunks recomputable").  Host side: argument
 // checks, the workspace plan, the dense projections and the launches of the
-// kernels in kv_recompute_kernels.hpp.  The projections of up to kHandGemmRows
+// kernels in kv_recompute_kernels.hpp.  The projections of up to kOwnGemmRows
 // recomputed tokens - what a plan of Eq. 4 recomputes beside a Load - run on the
 // library's own MFMA GEMM (kv_gemm_kernels.hpp); larger ones go to rocBLAS, which
 // is loaded at run time if it is there (the rest of the library does not depend
@@ -44,21 +44,19 @@ typedef int (*rb_get_solutions_fn)(rb_handle, int, int, int, int, int, const voi
                                    const void*, int, int, const void*, const void*, int, int, void*, int, int,
                                    int, int, uint32_t, int*, int*);
 
+// Measured on MI355X, a whole layer in us: own kernels / the GEMM library's standard choice above
+//   d_model 4096, 32 kv heads, d_ff 11008:  1024 rows 635 / 644   1536 rows 880 / 868   2048 rows 1091 / 1263
+//   d_model 4096,  8 kv heads, d_ff 14336:  2048 rows 1135 / 1093
+// (the library's choice varies with the shape; below, the own kernels are ahead everywhere: 512 rows 366, 348 us of
+// projections alone before them)
+constexpr int64_t kOwnGemmRows = KV_RECOMPUTE_OWN_GEMM_ROWS;
+
 uint64_t align256(uint64_t v) { return (v + 255) & ~static_cast<uint64_t>(255); }
 
 struct Plan {
     uint64_t xn, q32, k32, v32, q16, attn, x1, gate, up, part_o, part_ml, gemm_part, total;
     int splits;          // workgroups that share the key range of one attention row block (1: no split)
 };
-
-// Measured on MI355X (Llama-2-7B layer; the seven projections in us, the library's after kv_recompute_tune,
-// and the whole layer in ms):
-//   128 rows   own 164   library 266   layer 0.27 against 0.34
-//   256 rows   own 211   library 253   layer 0.32 against 0.35
-//   512 rows   own 349   library 363   layer 0.47 against 0.49
-//   1024 rows  own 640   library 474   layer 0.79 against 0.67
-//   4096 rows  own 2200 (750 TFLOP/s)   library 1420 (1.2-1.4 PFLOP/s)
-constexpr int64_t kHandGemmRows = KV_RECOMPUTE_OWN_GEMM_ROWS;
 
 // Up to three weight matrices [K][N[j]] applied to the same activations in one launch.
 struct GemmGroup {
@@ -68,34 +66,85 @@ struct GemmGroup {
     void* C[kGemmMaxMats];
 };
 
-// Launch shape of the library's own GEMM: row blocks per tile, K range per split, number of splits.
-struct HandGemm {
-    int mb, k_slice, splits;
-    uint32_t tiles_n, tiles_m;
-    uint64_t part_bytes;
+// Launch shape of the library's own GEMM: row blocks of 32 per workgroup, streamed or tiled, steps of K per
+// split, number of splits.
+struct OwnGemm {
+    int mb, steps, splits;
+    bool stream;
+    uint32_t col_tiles, row_tiles;
 };
 
-HandGemm hand_gemm_plan(int64_t M, const int64_t* N, int n_mats, int64_t K) {
-    HandGemm h;
-    h.mb = M <= 32 ? 1 : (M <= 64 ? 2 : 4);
-    h.tiles_n = 0;
+// Up to 64 rows the weights are streamed: as many splits (at most 8) as make some 640 workgroups of a row block
+// (two per CU and some: gate | up of a Llama-2-7B layer, 16 rows, 34 us with 4 splits, 36 with one) or 256 of two
+// (o, 64 rows, 14.0 us with 8 splits, 14.9 with 6; q | k | v 26 with 2).
+// Above, the row blocks per workgroup (3..8) and the splits that minimise
+//     rounds of 256 workgroups * steps * (0.13 + 0.045 * row blocks) us + 6 us, not less than the weights at
+//     4.8 TB/s, + writing and reading the partial products at 5 TB/s each,
+// with the cost of a step fitted to launches of 128 .. 4096 rows (row blocks 4, 5, 8: 0.31, 0.35, 0.49 us).
+// `room` bytes are there for partial products.
+OwnGemm own_gemm_plan(int64_t M, const int64_t* N, int n_mats, int64_t K, uint64_t room) {
+    OwnGemm best{};
     int64_t n_sum = 0;
+    for (int j = 0; j < n_mats; ++j) n_sum += N[j];
+    const int64_t steps = (K + kGemmStep - 1) / kGemmStep;
+    const int64_t part = M * n_sum * 4;                                  // bytes of one split's partial product
+    const int64_t room_splits = std::min<int64_t>(kGemmMaxSplits, static_cast<int64_t>(room / static_cast<uint64_t>(part)));
+    auto tiles = [&](int64_t cols) {
+        int64_t t = 0;
+        for (int j = 0; j < n_mats; ++j) t += (N[j] + cols - 1) / cols;
+        return t;
+    };
+    if (M <= 64) {
+        best.stream = true;
+        best.mb = M <= 32 ? 1 : 2;
+        best.col_tiles = static_cast<uint32_t>(tiles(kStreamCols));
+        best.row_tiles = 1;
+        int64_t s = (best.mb == 1 ? 640 : 256) / best.col_tiles;
+        s = std::max<int64_t>(1, std::min<int64_t>({s, 8, room_splits, steps / 16}));
+        best.steps = static_cast<int>((steps + s - 1) / s);
+        best.splits = static_cast<int>((steps + best.steps - 1) / best.steps);
+        return best;
+    }
+    double least = 0.0;
+    for (int mb = 3; mb <= 8; ++mb) {
+        const int64_t row_tiles = (M + 32 * mb - 1) / (32 * mb), groups = tiles(kTileCols) * row_tiles;
+        for (int64_t s = 1; s <= kGemmMaxSplits && (s == 1 || (s <= room_splits && steps / s >= 2 * kGemmStage)); ++s) {
+            const int64_t each = ((steps + s - 1) / s + kGemmStage - 1) / kGemmStage * kGemmStage;
+            const int64_t splits = (steps + each - 1) / each;
+            const double rounds = static_cast<double>((groups * splits + 255) / 256);
+            double us = rounds * static_cast<double>(each) * (0.13 + 0.045 * mb) + 6.0;
+            us = std::max(us, static_cast<double>(K * n_sum) * 2.0 / 4.8e6);
+            if (splits > 1) us += 2.0 * static_cast<double>(splits * part) / 5e6;
+            if (best.mb == 0 || us < least) {
+                least = us;
+                best.mb = mb;
+                best.steps = static_cast<int>(each);
+                best.splits = static_cast<int>(splits);
+                best.col_tiles = static_cast<uint32_t>(tiles(kTileCols));
+                best.row_tiles = static_cast<uint32_t>(row_tiles);
+            }
+        }
+    }
+    return best;
+}
+
+// Bytes set aside for partial products at the end of the workspace.  Part of what kv_recompute_workspace_bytes has
+// always promised, whatever the launches make of it: tiles of up to 128 x 128, K divided until some 256 (up to 128
+// rows) or 512 workgroups exist, at least 256 of K per split, the largest of a layer's four groups of projections.
+uint64_t partials_reserve(int64_t M, const int64_t* N, int n_mats, int64_t K) {
+    const int64_t rows = M <= 32 ? 32 : (M <= 64 ? 64 : 128);
+    int64_t tiles_n = 0, n_sum = 0;
     for (int j = 0; j < n_mats; ++j) {
-        h.tiles_n += static_cast<uint32_t>((N[j] + 127) / 128);
+        tiles_n += (N[j] + 127) / 128;
         n_sum += N[j];
     }
-    h.tiles_m = static_cast<uint32_t>((M + h.mb * 32 - 1) / (h.mb * 32));
-    // K is divided until some 512 workgroups exist (two per CU), at least 256 of K per split.  Up to 128
-    // rows 256 workgroups are as fast (measured: the four launches of a layer take 164-168 us with 256,
-    // 384, 512 and 768 workgroups) and leave half the partial products for the next kernel to add.
-    const int64_t tiles = static_cast<int64_t>(h.tiles_n) * h.tiles_m;
+    const int64_t tiles = tiles_n * ((M + rows - 1) / rows);
     const int64_t groups = M <= 128 ? 256 : 512;
     int64_t want = (groups + tiles - 1) / tiles;
     want = std::min<int64_t>(want, std::min<int64_t>(kGemmMaxSplits, std::max<int64_t>(1, K / 256)));
-    h.k_slice = static_cast<int>(((K + want - 1) / want + kGemmKStep - 1) / kGemmKStep * kGemmKStep);
-    h.splits = static_cast<int>((K + h.k_slice - 1) / h.k_slice);
-    h.part_bytes = h.splits > 1 ? static_cast<uint64_t>(h.splits) * M * n_sum * 4u : 0u;
-    return h;
+    const int64_t slice = ((K + want - 1) / want + 31) / 32 * 32;
+    const int64_t splits = (K + slice - 1) / slice;
+    return splits > 1 ? static_cast<uint64_t>(splits) * M * n_sum * 4u : 0u;
 }
 
 // With few recomputed rows the attention kernel has too few workgroups to fill 256 CUs: the key
@@ -132,13 +181,12 @@ Plan plan_workspace(const kv_shape_t& s, const kv_layer_dims_t& d, int64_t M) {
     if (p.splits > 1) o += align256(static_cast<uint64_t>(p.splits) * M * dq * 4u);
     p.part_ml = o;
     if (p.splits > 1) o += align256(static_cast<uint64_t>(p.splits) * M * s.n_q_heads * 8u);
-    // the library's own GEMM: partial tiles of the largest of its four launches
+    // the library's own GEMM: partial products
     const int64_t n_qkv[3] = {static_cast<int64_t>(dq), static_cast<int64_t>(dkv), static_cast<int64_t>(dkv)};
     const int64_t n_o[1] = {d.d_model}, n_ff[2] = {d.d_ff, d.d_ff};
-    const HandGemm hg[4] = {hand_gemm_plan(M, n_qkv, 3, d.d_model), hand_gemm_plan(M, n_o, 1, static_cast<int64_t>(dq)),
-                            hand_gemm_plan(M, n_ff, 2, d.d_model), hand_gemm_plan(M, n_o, 1, d.d_ff)};
-    uint64_t part = 0;
-    for (const HandGemm& h : hg) part = std::max(part, h.part_bytes);
+    const uint64_t part = std::max(
+        std::max(partials_reserve(M, n_qkv, 3, d.d_model), partials_reserve(M, n_o, 1, static_cast<int64_t>(dq))),
+        std::max(partials_reserve(M, n_ff, 2, d.d_model), partials_reserve(M, n_o, 1, d.d_ff)));
     p.gemm_part = o;
     o += align256(part);
     p.total = o;
@@ -197,23 +245,37 @@ int gemm_status(kv_recompute* rc, const GemmShape& g, const void* A, const void*
                        solution < 0 ? 0 : solution, 0);
 }
 
-// The library's own GEMM (kv_gemm_kernels.hpp) over a group of weight matrices; `part` holds what hand_gemm_plan
-// asks for.  With `splits_left` a product that was divided along K stays in `part` as *splits_left > 1 partial
-// products per matrix ([splits][M][N[j]], matrix after matrix) for the caller's next kernel to add; otherwise
-// (one matrix only) it is added here.
-int hand_gemm(hipStream_t st, int64_t M, int64_t K, const void* A, const GemmGroup& grp, const void* Cin,
-              bool out_f32, float* part, int* splits_left, const char* what) {
-    if (splits_left) *splits_left = 1;
-    if (!splits_left && grp.n != 1) return fail(KV_EINVAL, "GEMM (%s): a group is added by its reader", what);
+// Where a group's product may leave partial products: bytes [begin, end) of the workspace, free at that time.
+struct Room {
+    uint8_t* at;
+    uint64_t bytes;
+};
+Room larger(Room a, Room b) { return a.bytes >= b.bytes ? a : b; }
+
+// What became of a group's product: complete in the C matrices (splits == 1), or `splits` partial products per
+// matrix, matrix after matrix ([splits][M][N[j]] binary32), from `part` on, for the caller's next kernel to add.
+struct Product {
+    int splits;
+    const float* part;
+};
+
+enum class Out { kF32, kF16, kF16Fragments };
+
+// The library's own GEMM (kv_gemm_kernels.hpp) over a group of weight matrices; A in fragment order.  Without
+// `left` (one matrix only) a divided product is added here.
+int own_gemm(hipStream_t st, int64_t M, int64_t K, const void* A, const GemmGroup& grp, const void* Cin, Out out,
+             Room room, Product* left, const char* what) {
+    if (!left && grp.n != 1) return fail(KV_EINVAL, "GEMM (%s): a group is added by its reader", what);
     if (K % 8 || K < 8 || M < 1 || grp.n < 1 || grp.n > kGemmMaxMats || (Cin && grp.n != 1))
         return fail(KV_ESHAPE, "GEMM (%s): unsupported shape", what);
     for (int j = 0; j < grp.n; ++j)
         if (grp.N[j] % 8 || grp.N[j] < 8) return fail(KV_ESHAPE, "GEMM (%s) needs N a multiple of 8", what);
-    const HandGemm h = hand_gemm_plan(M, grp.N, grp.n, K);
+    const OwnGemm h = own_gemm_plan(M, grp.N, grp.n, K, room.bytes);
+    const int64_t cols = h.stream ? kStreamCols : kTileCols;
     GemmArgs g;
     g.A = static_cast<const _Float16*>(A);
     g.Cin = static_cast<const _Float16*>(Cin);
-    g.part = part;
+    g.part = reinterpret_cast<float*>(room.at);
     int32_t tiles = 0;
     uint64_t at = 0;
     for (int j = 0; j < kGemmMaxMats; ++j) {
@@ -223,38 +285,53 @@ int hand_gemm(hipStream_t st, int64_t M, int64_t K, const void* A, const GemmGro
         g.N[j] = static_cast<int32_t>(grp.N[k]);
         g.part_at[j] = at;
         if (j < grp.n) {
-            tiles += static_cast<int32_t>((grp.N[j] + 127) / 128);
+            tiles += static_cast<int32_t>((grp.N[j] + cols - 1) / cols);
             at += static_cast<uint64_t>(h.splits) * M * grp.N[j];
         }
         g.tile_end[j] = tiles;
     }
     g.M = static_cast<int32_t>(M);
     g.K = static_cast<int32_t>(K);
-    g.k_slice = h.k_slice;
+    g.steps = h.steps;
     g.splits = h.splits;
-    g.out_f32 = out_f32 ? 1 : 0;
-    const dim3 grid(h.tiles_n, static_cast<uint32_t>(h.splits), h.tiles_m);
-    if (h.mb == 1) hipLaunchKernelGGL(gemm_f16_kernel<1>, grid, dim3(256), 0, st, g);
-    else if (h.mb == 2) hipLaunchKernelGGL(gemm_f16_kernel<2>, grid, dim3(256), 0, st, g);
-    else hipLaunchKernelGGL(gemm_f16_kernel<4>, grid, dim3(256), 0, st, g);
-    if (h.splits > 1) {
-        if (splits_left) *splits_left = h.splits;
-        else hipLaunchKernelGGL(gemm_reduce_kernel, dim3(static_cast<uint32_t>((M * grp.N[0] / 4 + 255) / 256)),
-                                dim3(256), 0, st, g);
+    g.out_f32 = out == Out::kF32 ? 1 : 0;
+    g.out_fragments = out == Out::kF16Fragments ? 1 : 0;
+    if (h.stream) {
+        const dim3 grid(h.col_tiles, static_cast<uint32_t>(h.splits), h.row_tiles);
+        if (h.mb == 1) hipLaunchKernelGGL(gemm_stream_kernel<1>, grid, dim3(256), 0, st, g);
+        else hipLaunchKernelGGL(gemm_stream_kernel<2>, grid, dim3(256), 0, st, g);
+    } else {
+        const int64_t blocks = static_cast<int64_t>((h.col_tiles + 7) / 8 * 8) * h.row_tiles;
+        if (blocks > 0x7fffffffLL) return fail(KV_ESHAPE, "GEMM (%s): grid exceeds 2^31 workgroups", what);
+        const dim3 grid(static_cast<uint32_t>(blocks), static_cast<uint32_t>(h.splits));
+        switch (h.mb) {
+            case 3: hipLaunchKernelGGL(gemm_tile_kernel<3>, grid, dim3(256), 0, st, g); break;
+            case 4: hipLaunchKernelGGL(gemm_tile_kernel<4>, grid, dim3(256), 0, st, g); break;
+            case 5: hipLaunchKernelGGL(gemm_tile_kernel<5>, grid, dim3(256), 0, st, g); break;
+            case 6: hipLaunchKernelGGL(gemm_tile_kernel<6>, grid, dim3(256), 0, st, g); break;
+            case 7: hipLaunchKernelGGL(gemm_tile_kernel<7>, grid, dim3(256), 0, st, g); break;
+            default: hipLaunchKernelGGL(gemm_tile_kernel<8>, grid, dim3(256), 0, st, g); break;
+        }
     }
+    if (left) *left = {h.splits, reinterpret_cast<const float*>(room.at)};
+    else if (h.splits > 1)
+        hipLaunchKernelGGL(gemm_reduce_kernel, dim3(static_cast<uint32_t>((M * grp.N[0] / 4 + 255) / 256)), dim3(256), 0, st, g);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail(KV_EHIP, "gemm_f16_kernel launch (%s): %s", what, hipGetErrorString(e));
+    if (e != hipSuccess) return fail(KV_EHIP, "GEMM launch (%s): %s", what, hipGetErrorString(e));
     return KV_OK;
 }
 
-// The projections of a group: one launch of the library's own kernel, or one GEMM of the library per matrix.
-int gemm(kv_recompute* rc, hipStream_t stream, float* part, int* splits_left, int64_t M, int64_t K, const void* A,
-         const GemmGroup& grp, const void* Cin, bool out_f32, const char* what) {
-    if (M <= kHandGemmRows || !rc->gemm_ex)
-        return hand_gemm(stream, M, K, A, grp, Cin, out_f32, part, splits_left, what);
-    if (splits_left) *splits_left = 1;
+// Whether the projections of M rows run on the library's own kernels.
+bool own_projections(const kv_recompute* rc, int64_t M) { return M <= kOwnGemmRows || !rc->gemm_ex; }
+
+// The projections of a group: one launch of the library's own kernel (A in fragment order), or one GEMM of the
+// library per matrix (A and the results row-major).
+int gemm(kv_recompute* rc, hipStream_t stream, int64_t M, int64_t K, const void* A, const GemmGroup& grp, const void* Cin,
+         Out out, Room room, Product* left, const char* what) {
+    if (own_projections(rc, M)) return own_gemm(stream, M, K, A, grp, Cin, out, room, left, what);
+    if (left) *left = {1, nullptr};
     for (int j = 0; j < grp.n; ++j) {
-        const GemmShape g = {M, grp.N[j], K, out_f32, Cin != nullptr};
+        const GemmShape g = {M, grp.N[j], K, out == Out::kF32, Cin != nullptr};
         int solution = -1;
         for (const auto& t : rc->tuned)
             if (t.first == g) solution = t.second;
@@ -431,7 +508,7 @@ int32_t kv_recompute_tune(kv_recompute_t* rc, const kv_shape_t* shape, const kv_
         return fail(KV_ENOMEM, "workspace %llu bytes, %llu needed", static_cast<unsigned long long>(workspace_bytes),
                     static_cast<unsigned long long>(p.total));
     // projections of few rows run on the library's own kernel; nothing to choose there, nor without a GEMM library
-    if (M <= kHandGemmRows || !rc->gemm_ex || !rc->get_solutions) return KV_OK;
+    if (own_projections(rc, M) || !rc->get_solutions) return KV_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (rc->set_stream(rc->handle, st) != 0) return fail(KV_EHIP, "rocblas_set_stream failed");
     // operands of ordinary magnitude and varied bits in every buffer a GEMM reads
@@ -494,11 +571,11 @@ int32_t kv_recompute_layer(kv_recompute_t* rc, const kv_shape_t* shape, const kv
         return fail(KV_ENOMEM, "workspace %llu bytes, %llu needed", static_cast<unsigned long long>(workspace_bytes),
                     static_cast<unsigned long long>(p.total));
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (rc->gemm_ex && M > kHandGemmRows && rc->set_stream(rc->handle, st) != 0)
+    const bool own = own_projections(rc, M);
+    if (!own && rc->set_stream(rc->handle, st) != 0)
         return fail(KV_EHIP, "rocblas_set_stream failed");
 
     uint8_t* base = static_cast<uint8_t*>(workspace);
-    float* gpart = reinterpret_cast<float*>(base + p.gemm_part);
     _Float16* xn = reinterpret_cast<_Float16*>(base + p.xn);
     float* q32 = reinterpret_cast<float*>(base + p.q32);
     float* k32 = reinterpret_cast<float*>(base + p.k32);
@@ -513,24 +590,26 @@ int32_t kv_recompute_layer(kv_recompute_t* rc, const kv_shape_t* shape, const kv
     const int64_t dq = static_cast<int64_t>(Hq) * D, dkv = static_cast<int64_t>(Hkv) * D;
     _Float16* k_plane = static_cast<_Float16*>(kv) + (static_cast<int64_t>(layer) * 2 + 0) * Hkv * s.n_tokens * D;
     _Float16* v_plane = k_plane + static_cast<int64_t>(Hkv) * s.n_tokens * D;
-    const dim3 rows(static_cast<uint32_t>((M + 3) / 4));
+    const dim3 rows(static_cast<uint32_t>(M));
+    const int32_t m32 = static_cast<int32_t>(M);
+    auto room = [&](uint64_t begin, uint64_t end) { return Room{base + begin, end - begin}; };
+    const _Float16 *norm1 = static_cast<const _Float16*>(w->w_norm1), *norm2 = static_cast<const _Float16*>(w->w_norm2);
 
     // 1. norm, q/k/v projections (binary32 results, rounded once after the rotation)
-    // (a product whose K range was divided stays in `gpart` as partial products, which the next kernel adds)
-    const float* no_part = nullptr;
-    hipLaunchKernelGGL(rmsnorm_kernel, rows, dim3(256), 0, st, xin, static_cast<const _Float16*>(w->w_norm1), xn,
-                       static_cast<int32_t>(M), dims->d_model, dims->rms_eps);
-    int sp = 1;
+    if (own) hipLaunchKernelGGL((rmsnorm_kernel<false, true>), rows, dim3(256), 0, st, nullptr, 1, xin, nullptr, norm1, xn, m32, dims->d_model, dims->rms_eps);
+    else hipLaunchKernelGGL((rmsnorm_kernel<false, false>), rows, dim3(256), 0, st, nullptr, 1, xin, nullptr, norm1, xn, m32, dims->d_model, dims->rms_eps);
+    Product pr;
     const GemmGroup qkv = {3, {dq, dkv, dkv}, {w->wq, w->wk, w->wv}, {q32, k32, v32}};
-    if (int e = gemm(rc, st, gpart, &sp, M, dims->d_model, xn, qkv, nullptr, true, "q | k | v")) return e;
-    const float* q_src = sp > 1 ? gpart : q32;
-    const float* k_src = sp > 1 ? gpart + sp * M * dq : k32;
-    const float* v_src = sp > 1 ? gpart + sp * M * (dq + dkv) : v32;
+    // (partial products behind q16, which the rotary kernel writes while it adds them)
+    if (int e = gemm(rc, st, M, dims->d_model, xn, qkv, nullptr, Out::kF32, room(p.attn, p.total), &pr, "q | k | v")) return e;
+    const float* q_src = pr.splits > 1 ? pr.part : q32;
+    const float* k_src = pr.splits > 1 ? pr.part + pr.splits * M * dq : k32;
+    const float* v_src = pr.splits > 1 ? pr.part + pr.splits * M * (dq + dkv) : v32;
     // 2. global position encoding; the recomputed K/V go to their places in the cache
     RopeTable tab;
     for (int i = 0; i < D / 2; ++i) tab.theta[i] = std::pow(static_cast<double>(dims->rope_base), -2.0 * i / D);
     hipLaunchKernelGGL(rope_scatter_kernel, dim3(static_cast<uint32_t>(M), 4), dim3(256), 0, st, q_src, k_src, v_src,
-                       chunk_idx_dev, q16, k_plane, v_plane, tab, s.chunk_tokens, s.n_tokens, Hq, Hkv, D, sp);
+                       chunk_idx_dev, q16, k_plane, v_plane, tab, s.chunk_tokens, s.n_tokens, Hq, Hkv, D, pr.splits);
     // 3. causal attention over the recovered K/V
     AttnGeom g;
     g.M = static_cast<int32_t>(M);
@@ -540,6 +619,7 @@ int32_t kv_recompute_layer(kv_recompute_t* rc, const kv_shape_t* shape, const kv
     g.Hkv = Hkv;
     g.n_rb = static_cast<int32_t>((M + 31) / 32);
     g.pairs = (Hq / Hkv) * g.n_rb;
+    g.fragments = own ? 1 : 0;
     g.scale_log2e = static_cast<float>(1.4426950408889634 / std::sqrt(static_cast<double>(D)));
     const uint32_t pair_blocks = static_cast<uint32_t>((g.pairs + kAttnWaves - 1) / kAttnWaves);
     if (p.splits > 1) {
@@ -553,12 +633,12 @@ int32_t kv_recompute_layer(kv_recompute_t* rc, const kv_shape_t* shape, const kv
             hipLaunchKernelGGL((recompute_attention_kernel<64, true>), agrid, dim3(64 * kAttnWaves), 0, st, q16,
                                k_plane, v_plane, chunk_idx_dev, attn, g, part_o, part_ml, per_split);
             hipLaunchKernelGGL(attention_combine_kernel<64>, dim3(static_cast<uint32_t>((rows * 16 + 255) / 256)),
-                               dim3(256), 0, st, part_o, part_ml, attn, rows, p.splits);
+                               dim3(256), 0, st, part_o, part_ml, attn, rows, p.splits, Hq, g.fragments);
         } else {
             hipLaunchKernelGGL((recompute_attention_kernel<128, true>), agrid, dim3(64 * kAttnWaves), 0, st, q16,
                                k_plane, v_plane, chunk_idx_dev, attn, g, part_o, part_ml, per_split);
             hipLaunchKernelGGL(attention_combine_kernel<128>, dim3(static_cast<uint32_t>((rows * 32 + 255) / 256)),
-                               dim3(256), 0, st, part_o, part_ml, attn, rows, p.splits);
+                               dim3(256), 0, st, part_o, part_ml, attn, rows, p.splits, Hq, g.fragments);
         }
     } else {
         const dim3 agrid(pair_blocks, static_cast<uint32_t>(Hkv));
@@ -571,21 +651,25 @@ int32_t kv_recompute_layer(kv_recompute_t* rc, const kv_shape_t* shape, const kv
     }
     // 4. output projection + residual, feed-forward + residual
     const GemmGroup og = {1, {dims->d_model}, {w->wo}, {x1}};
-    if (int e = gemm(rc, st, gpart, &sp, M, dq, attn, og, xin, false, "o")) return e;
-    if (sp > 1)
-        hipLaunchKernelGGL(rmsnorm_sum_kernel, dim3(static_cast<uint32_t>(M)), dim3(256), 0, st, gpart, sp, xin, x1,
-                           static_cast<const _Float16*>(w->w_norm2), xn, static_cast<int32_t>(M), dims->d_model,
-                           dims->rms_eps);
+    // (free but for xn and x1, which the norm writes while it adds the partial products)
+    if (int e = gemm(rc, st, M, dq, attn, og, xin, Out::kF16, larger(room(p.q32, p.attn), room(p.gate, p.total)), &pr, "o")) return e;
+    if (pr.splits > 1)
+        hipLaunchKernelGGL((rmsnorm_kernel<true, true>), rows, dim3(256), 0, st, pr.part, pr.splits, xin, x1, norm2, xn, m32, dims->d_model, dims->rms_eps);
+    else if (own)
+        hipLaunchKernelGGL((rmsnorm_kernel<false, true>), rows, dim3(256), 0, st, nullptr, 1, x1, nullptr, norm2, xn, m32, dims->d_model, dims->rms_eps);
     else
-        hipLaunchKernelGGL(rmsnorm_kernel, rows, dim3(256), 0, st, x1, static_cast<const _Float16*>(w->w_norm2), xn,
-                           static_cast<int32_t>(M), dims->d_model, dims->rms_eps);
+        hipLaunchKernelGGL((rmsnorm_kernel<false, false>), rows, dim3(256), 0, st, nullptr, 1, x1, nullptr, norm2, xn, m32, dims->d_model, dims->rms_eps);
     const GemmGroup ff = {2, {dims->d_ff, dims->d_ff}, {w->w_gate, w->w_up}, {gate, up}};
-    if (int e = gemm(rc, st, gpart, &sp, M, dims->d_model, xn, ff, nullptr, false, "gate | up")) return e;
-    const int64_t n8 = M * dims->d_ff / 8;
+    // (the activation goes to `gate`)
+    if (int e = gemm(rc, st, M, dims->d_model, xn, ff, nullptr, own ? Out::kF16Fragments : Out::kF16,
+                     larger(room(p.q32, p.x1), room(p.part_o, p.total)), &pr, "gate | up")) return e;
+    const int64_t n8 = M * (dims->d_ff / 8);
+    const float* no_part = nullptr;
     hipLaunchKernelGGL(silu_mul_kernel, dim3(static_cast<uint32_t>((n8 + 255) / 256)), dim3(256), 0, st, gate, up,
-                       gate, n8, sp > 1 ? gpart : no_part, sp > 1 ? gpart + sp * M * dims->d_ff : no_part, sp);
+                       gate, m32, dims->d_ff, pr.splits > 1 ? pr.part : no_part,
+                       pr.splits > 1 ? pr.part + pr.splits * M * dims->d_ff : no_part, pr.splits, own ? 1 : 0);
     const GemmGroup down = {1, {dims->d_model}, {w->w_down}, {x_out}};
-    if (int e = gemm(rc, st, gpart, nullptr, M, dims->d_ff, gate, down, x1, false, "down")) return e;
+    if (int e = gemm(rc, st, M, dims->d_ff, gate, down, x1, Out::kF16, larger(room(p.xn, p.x1), room(p.up, p.total)), nullptr, "down")) return e;
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(KV_EHIP, "recompute launch: %s", hipGetErrorString(e));
     return KV_OK;

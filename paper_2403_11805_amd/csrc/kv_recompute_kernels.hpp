@@ -3,12 +3,13 @@
 // one Llama-style block; q and k are encoded with the tokens' GLOBAL positions,
 // the recomputed K/V are inserted between the resident K/V of the cache, and the
 // recomputed queries attend to the recovered K/V under a causal mask by global
-// position.  The dense projections are library GEMMs; everything else is here.
+// position.  The dense projections are in kv_gemm_kernels.hpp; everything else is here.
 #pragma once
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "kv_gemm_kernels.hpp"
 #include "kv_lane_ops.hpp"
 
 namespace kvs {
@@ -26,75 +27,66 @@ __device__ __forceinline__ int global_position(const int32_t* __restrict__ chunk
 }
 
 // xn[m][:] = x[m][:] / sqrt(mean(x[m][:]^2) + eps) * w[:]      (fp16 in/out, binary32 inside)
-// One wavefront per row; d_model % 8 == 0.
-__global__ __launch_bounds__(256) void rmsnorm_kernel(const _Float16* __restrict__ x,
-                                                      const _Float16* __restrict__ w,
-                                                      _Float16* __restrict__ xn, int32_t M,
-                                                      int32_t d_model, float eps) {
-    const int lane = threadIdx.x & 63;
-    const int m = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (m >= M) return;
-    const rv8h_t* row = reinterpret_cast<const rv8h_t*>(x + static_cast<int64_t>(m) * d_model);
-    const int pieces = d_model / 8;
-    float ss = 0.0f;
-    for (int p = lane; p < pieces; p += 64) {
-        const rv8h_t v = row[p];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) ss += static_cast<float>(v[k]) * static_cast<float>(v[k]);
-    }
-#pragma unroll
-    for (int o = 16; o >= 1; o >>= 1) ss += __shfl_xor(ss, o);
-    ss = xhalf_sum(ss);
-    const float r = 1.0f / sqrtf(ss / static_cast<float>(d_model) + eps);
-    const rv8h_t* wp = reinterpret_cast<const rv8h_t*>(w);
-    rv8h_t* out = reinterpret_cast<rv8h_t*>(xn + static_cast<int64_t>(m) * d_model);
-    for (int p = lane; p < pieces; p += 64) {
-        const rv8h_t v = row[p], g = wp[p];
-        rv8h_t o;
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-            o[k] = static_cast<_Float16>(static_cast<float>(v[k]) * r * static_cast<float>(g[k]));
-        out[p] = o;
-    }
+// FRAGMENTS: xn is written in the GEMM kernels' fragment order, otherwise row-major.  SUM: the row is first made
+// from what a projection left as `splits` binary32 partial products [splits][M][d_model]:
+// x[m][:] = fp16(part[0][m][:] + part[1][m][:] + ... + resid[m][:])  (split order, rounded once) is stored - it is
+// the next residual - and normed; otherwise resid is the row and x is not written.  One workgroup per row: with a
+// wavefront per row its loads come in eight dependent trips (16 rows of 4096: 9.3 us).  d_model % 8 == 0; up to
+// kNormPieces * 2048 elements of a row stay in registers, a longer row is read (SUM: from x) a second time.
+constexpr int kNormPieces = 2;
+// Row of a workgroup that writes one row in fragment order: its pieces share 128-byte lines with those of the rows
+// beside it, so the 32 rows of a block go to workgroups of one XCD (ids are dealt to the eight in turn), in whose
+// L2 the lines fill up.  (2048 rows of 4096: 11.0 us, 18.3 with row = id.)
+__device__ __forceinline__ int fragment_row(int id, int M) {
+    if (id >= M / 256 * 256) return id;
+    const int in = id & 255;
+    return (id - in) + (in & 7) * 32 + (in >> 3);
 }
-
-// The same norm over a row that a projection left as `splits` binary32 partial products
-// [splits][M][d_model]:  x[m][:] = fp16(part[0][m][:] + part[1][m][:] + ... + resid[m][:])  (split order,
-// rounded once) is stored - it is the next residual - and normed.  One workgroup per row: with few rows
-// the partial products are most of what a layer reads here, and a wavefront per row would leave the
-// memory system idle.
-__global__ __launch_bounds__(256) void rmsnorm_sum_kernel(const float* __restrict__ part, int32_t splits,
-                                                          const _Float16* __restrict__ resid,
-                                                          _Float16* __restrict__ x,
-                                                          const _Float16* __restrict__ w,
-                                                          _Float16* __restrict__ xn, int32_t M,
-                                                          int32_t d_model, float eps) {
+template <bool SUM, bool FRAGMENTS>
+__global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ part, int32_t splits,
+                                                      const _Float16* __restrict__ resid, _Float16* __restrict__ x,
+                                                      const _Float16* __restrict__ w, _Float16* __restrict__ xn,
+                                                      int32_t M, int32_t d_model, float eps) {
     __shared__ float wave_ss[4];
-    const int m = blockIdx.x;
+    const int m = FRAGMENTS ? fragment_row(blockIdx.x, M) : static_cast<int>(blockIdx.x);
     const int pieces = d_model / 8;
-    const int64_t plane4 = static_cast<int64_t>(M) * d_model / 4;
-    const rv4f_t* src = reinterpret_cast<const rv4f_t*>(part) + static_cast<int64_t>(m) * d_model / 4;
     const rv8h_t* res = reinterpret_cast<const rv8h_t*>(resid + static_cast<int64_t>(m) * d_model);
-    rv8h_t* row = reinterpret_cast<rv8h_t*>(x + static_cast<int64_t>(m) * d_model);
-    float ss = 0.0f;
-    for (int p = threadIdx.x; p < pieces; p += 256) {
-        rv4f_t lo = src[2 * p], hi = src[2 * p + 1];
+    rv8h_t* row = SUM ? reinterpret_cast<rv8h_t*>(x + static_cast<int64_t>(m) * d_model) : nullptr;
+    auto piece = [&](int p) __attribute__((always_inline)) {
+        rv8h_t v = res[p];
+        if constexpr (SUM) {
+            const int64_t plane4 = static_cast<int64_t>(M) * d_model / 4;
+            const rv4f_t* src = reinterpret_cast<const rv4f_t*>(part) + static_cast<int64_t>(m) * d_model / 4 + 2 * p;
+            rv4f_t lo = src[0], hi = src[1];
 #pragma unroll 4
-        for (int sp = 1; sp < splits; ++sp) {
-            lo += src[sp * plane4 + 2 * p];
-            hi += src[sp * plane4 + 2 * p + 1];
-        }
-        const rv8h_t r = res[p];
-        rv8h_t v;
+            for (int sp = 1; sp < splits; ++sp) {
+                lo += src[sp * plane4];
+                hi += src[sp * plane4 + 1];
+            }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            v[k] = static_cast<_Float16>(lo[k] + static_cast<float>(r[k]));
-            v[k + 4] = static_cast<_Float16>(hi[k] + static_cast<float>(r[k + 4]));
+            for (int k = 0; k < 4; ++k) {
+                v[k] = static_cast<_Float16>(lo[k] + static_cast<float>(v[k]));
+                v[k + 4] = static_cast<_Float16>(hi[k] + static_cast<float>(v[k + 4]));
+            }
+            row[p] = v;                              // read again below, if at all, by this same thread
         }
-        row[p] = v;                                  // read again below by this same thread
+        return v;
+    };
+    float ss = 0.0f;
+    auto square = [&](const rv8h_t& v) __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < 8; ++k) ss += static_cast<float>(v[k]) * static_cast<float>(v[k]);
+    };
+    rv8h_t held[kNormPieces];
+#pragma unroll
+    for (int i = 0; i < kNormPieces; ++i) {
+        const int p = i * 256 + static_cast<int>(threadIdx.x);
+        if (p < pieces) {
+            held[i] = piece(p);
+            square(held[i]);
+        }
     }
+    for (int p = kNormPieces * 256 + threadIdx.x; p < pieces; p += 256) square(piece(p));
 #pragma unroll
     for (int o = 16; o >= 1; o >>= 1) ss += __shfl_xor(ss, o);
     ss = xhalf_sum(ss);
@@ -103,15 +95,21 @@ __global__ __launch_bounds__(256) void rmsnorm_sum_kernel(const float* __restric
     ss = (wave_ss[0] + wave_ss[1]) + (wave_ss[2] + wave_ss[3]);
     const float r = 1.0f / sqrtf(ss / static_cast<float>(d_model) + eps);
     const rv8h_t* wp = reinterpret_cast<const rv8h_t*>(w);
-    rv8h_t* out = reinterpret_cast<rv8h_t*>(xn + static_cast<int64_t>(m) * d_model);
-    for (int p = threadIdx.x; p < pieces; p += 256) {
-        const rv8h_t v = row[p], g = wp[p];
+    auto scaled = [&](int p, const rv8h_t& v) __attribute__((always_inline)) {
+        const rv8h_t g = wp[p];
         rv8h_t o;
 #pragma unroll
         for (int k = 0; k < 8; ++k)
             o[k] = static_cast<_Float16>(static_cast<float>(v[k]) * r * static_cast<float>(g[k]));
-        out[p] = o;
+        const int64_t at = FRAGMENTS ? fragment_at(m, 8 * p, M, d_model) : static_cast<int64_t>(m) * d_model + 8 * p;
+        *reinterpret_cast<rv8h_t*>(xn + at) = o;
+    };
+#pragma unroll
+    for (int i = 0; i < kNormPieces; ++i) {
+        const int p = i * 256 + static_cast<int>(threadIdx.x);
+        if (p < pieces) scaled(p, held[i]);
     }
+    for (int p = kNormPieces * 256 + threadIdx.x; p < pieces; p += 256) scaled(p, SUM ? row[p] : res[p]);
 }
 
 // Rotary angles: theta[i] = base^(-2i/D) in double, computed on the host.
@@ -193,16 +191,27 @@ __global__ __launch_bounds__(256) void rope_scatter_kernel(const float* __restri
     }
 }
 
-// act = silu(gate) * up, elementwise, 8 elements per thread (n % 8 == 0).
-// (act may be gate: each thread reads its elements before it writes them)
-// With `part_gate` the two operands are first made from projections left as `splits` binary32 partial
-// products of n8 * 8 elements each: gate = fp16(sum in split order), up likewise.
-__global__ __launch_bounds__(256) void silu_mul_kernel(const _Float16* gate, const _Float16* up,
-                                                       _Float16* act, int64_t n8,
-                                                       const float* __restrict__ part_gate,
-                                                       const float* __restrict__ part_up, int32_t splits) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n8) return;
+// act[M][d_ff] = silu(gate) * up, 8 elements per thread (d_ff % 8 == 0); the three have one layout, row-major or
+// fragment order, and act may be gate (each thread reads its elements before it writes them).
+// With `part_gate` the two operands are instead made from projections left as `splits` binary32 partial products
+// [splits][M][d_ff]: gate = fp16(sum in split order), up likewise; with `fragments` act is then written in fragment
+// order, the threads following it (32 rows side by side: a workgroup writes consecutive pieces, and the eight pieces
+// it reads of a row fill a 256-byte line).
+__global__ __launch_bounds__(256) void silu_mul_kernel(const _Float16* gate, const _Float16* up, _Float16* act, int32_t M,
+                                                       int32_t d_ff, const float* __restrict__ part_gate,
+                                                       const float* __restrict__ part_up, int32_t splits, int32_t fragments) {
+    const int64_t id = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    const int64_t n8 = static_cast<int64_t>(M) * (d_ff / 8);
+    if (id >= n8) return;
+    int64_t i = id;
+    if (part_gate && fragments) {                    // the row-major piece that belongs to piece `id` of the result
+        const int per_row = d_ff / 8;
+        const int b = static_cast<int>(id / (32 * per_row));
+        const int in = static_cast<int>(id - static_cast<int64_t>(b) * 32 * per_row);
+        const int rows = min(32, M - 32 * b);
+        const int k8 = in / rows;
+        i = static_cast<int64_t>(32 * b + in - k8 * rows) * per_row + k8;
+    }
     rv8h_t g, u;
     if (part_gate) {
         const rv4f_t* pg = reinterpret_cast<const rv4f_t*>(part_gate);
@@ -228,7 +237,7 @@ __global__ __launch_bounds__(256) void silu_mul_kernel(const _Float16* gate, con
         const float x = static_cast<float>(g[k]);
         o[k] = static_cast<_Float16>(x / (1.0f + __expf(-x)) * static_cast<float>(u[k]));
     }
-    reinterpret_cast<rv8h_t*>(act)[i] = o;
+    reinterpret_cast<rv8h_t*>(act)[id] = o;
 }
 
 // Stand-in operands for timing GEMM kernels: every 16-bit half is a binary16 of magnitude
@@ -249,6 +258,7 @@ struct AttnGeom {
     int32_t Hq, Hkv;
     int32_t n_rb;     // ceil(M / 32): blocks of 32 query rows
     int32_t pairs;    // (Hq / Hkv) * n_rb: (row block, query head) pairs per kv head
+    int32_t fragments; // 1: the output is written in the GEMM kernels' fragment order
     float scale_log2e;
 };
 
@@ -467,7 +477,9 @@ __global__ __launch_bounds__(64 * kAttnWaves) void recompute_attention_kernel(
     if (ok) {
         // o_acc[b][v]: head dimension 32*b + 8*(v/4) + 4*half + v%4 of this lane's query row
         const float inv = 1.0f / l_run;         // a row sees at least its own token
-        _Float16* dst = out + (static_cast<int64_t>(m) * g.Hq + head) * D;
+        // row-major, or in fragment order: rows side by side, eight head dimensions per piece
+        const int piece = g.fragments ? min(32, g.M - rb * 32) * 8 : 8;
+        _Float16* dst = out + (g.fragments ? fragment_at(m, head * D, g.M, g.Hq * D) : (static_cast<int64_t>(m) * g.Hq + head) * D);
 #pragma unroll
         for (int b = 0; b < DB; ++b)
 #pragma unroll
@@ -475,7 +487,7 @@ __global__ __launch_bounds__(64 * kAttnWaves) void recompute_attention_kernel(
                 rv4h_t o4;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) o4[k] = static_cast<_Float16>(o_acc[b][4 * j + k] * inv);
-                *reinterpret_cast<rv4h_t*>(dst + 32 * b + 8 * j + 4 * half) = o4;
+                *reinterpret_cast<rv4h_t*>(dst + (4 * b + j) * piece + 4 * half) = o4;
             }
     }
 }
@@ -486,7 +498,7 @@ template <int D>
 __global__ __launch_bounds__(256) void attention_combine_kernel(const float* __restrict__ part_o,
                                                                 const float* __restrict__ part_ml,
                                                                 _Float16* __restrict__ out, int64_t rows,
-                                                                int n_splits) {
+                                                                int n_splits, int Hq, int fragments) {
     constexpr int kQuads = D / 4;
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= rows * kQuads) return;
@@ -528,7 +540,12 @@ __global__ __launch_bounds__(256) void attention_combine_kernel(const float* __r
     rv4h_t o4;
 #pragma unroll
     for (int k = 0; k < 4; ++k) o4[k] = static_cast<_Float16>(acc[k] * inv);
-    *reinterpret_cast<rv4h_t*>(out + row * D + quad * 4) = o4;
+    int64_t at = row * D + quad * 4;
+    if (fragments) {
+        const int m = static_cast<int>(row / Hq), head = static_cast<int>(row - static_cast<int64_t>(m) * Hq);
+        at = fragment_at(m, head * D + quad * 4, static_cast<int>(rows / Hq), Hq * D);
+    }
+    *reinterpret_cast<rv4h_t*>(out + at) = o4;
 }
 
 }  // namespace kvs
