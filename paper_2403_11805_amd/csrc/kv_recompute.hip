@@ -54,8 +54,7 @@ constexpr int64_t kOwnGemmRows = KV_RECOMPUTE_OWN_GEMM_ROWS;
 uint64_t align256(uint64_t v) { return (v + 255) & ~static_cast<uint64_t>(255); }
 
 struct Plan {
-    uint64_t xn, q32, k32, v32, q16, attn, x1, gate, up, part_o, part_ml, gemm_part, total;
-    int splits;          // workgroups that share the key range of one attention row block (1: no split)
+    uint64_t xn, q32, k32, v32, q16, attn, x1, gate, up, part_o, total;
 };
 
 // Up to three weight matrices [K][N[j]] applied to the same activations in one launch.
@@ -147,18 +146,33 @@ uint64_t partials_reserve(int64_t M, const int64_t* N, int n_mats, int64_t K) {
     return splits > 1 ? static_cast<uint64_t>(splits) * M * n_sum * 4u : 0u;
 }
 
-// With few recomputed rows the attention kernel has too few workgroups to fill 256 CUs: the key
-// range is then divided among up to 16 workgroups (one workgroup per CU in total: measured, more
-// shares cost more in partial results than they gain; at least four key tiles per share, at most
-// 64 MiB of partial results).
-int attention_splits(const kv_shape_t& s, int64_t M) {
+// With few recomputed rows the attention kernel has too few workgroups to fill 256 CUs: the key ranges are then
+// divided (at least four key tiles per share over the whole cache), as far as there is room for the shares, until
+// some 512 workgroups exist (two per CU; 768 cost more in partial results than they gain: 512 rows, 32 heads, 356
+// against 344 us per layer).  More than eight shares only where eight do not make 256 workgroups: 128 rows, 32 heads
+// 182 us with 8, 188 with 16, 190 with 4; 4 kv heads, 16 rows 52 us with 16, 53 with 8.
+uint64_t attention_share_bytes(const kv_shape_t& s, int64_t M) {
+    return static_cast<uint64_t>(M) * s.n_q_heads * (s.head_dim + 2) * 4;
+}
+int attention_splits(const kv_shape_t& s, int64_t M, uint64_t room) {
     const int64_t pairs = static_cast<int64_t>(s.n_q_heads / s.n_kv_heads) * ((M + 31) / 32);
     const int64_t base = (pairs + kAttnWaves - 1) / kAttnWaves * s.n_kv_heads;
+    int64_t splits = 512 / base;
+    if (splits > 8) splits = std::max<int64_t>(8, std::min<int64_t>(kMaxSplits, 256 / base));
+    splits = std::min<int64_t>(splits, (s.n_tokens + 31) / 32 / 4);
+    splits = std::min<int64_t>(splits, static_cast<int64_t>(room / attention_share_bytes(s, M)));
+    return static_cast<int>(std::max<int64_t>(splits, 1));
+}
+
+// Shares that the workspace has a place of their own for.  Part of what kv_recompute_workspace_bytes has always
+// promised, whatever the launch makes of it (eight pairs per workgroup, 256 workgroups, at most 64 MiB).
+int attention_reserve(const kv_shape_t& s, int64_t M) {
+    const int64_t pairs = static_cast<int64_t>(s.n_q_heads / s.n_kv_heads) * ((M + 31) / 32);
+    const int64_t base = (pairs + 7) / 8 * s.n_kv_heads;
     int64_t splits = 256 / base;
     splits = std::min<int64_t>(splits, (s.n_tokens + 31) / 32 / 4);
-    splits = std::min<int64_t>(splits, kMaxSplits);
-    const int64_t per_split = M * s.n_q_heads * (s.head_dim + 2) * 4;
-    splits = std::min<int64_t>(splits, (64ll << 20) / per_split);
+    splits = std::min<int64_t>(splits, 16);
+    splits = std::min<int64_t>(splits, (64ll << 20) / static_cast<int64_t>(attention_share_bytes(s, M)));
     return static_cast<int>(std::max<int64_t>(splits, 1));
 }
 
@@ -176,18 +190,18 @@ Plan plan_workspace(const kv_shape_t& s, const kv_layer_dims_t& d, int64_t M) {
     p.x1 = o;   o += align256(M * d.d_model * 2u);
     p.gate = o; o += align256(M * static_cast<uint64_t>(d.d_ff) * 2u);
     p.up = o;   o += align256(M * static_cast<uint64_t>(d.d_ff) * 2u);
-    p.splits = attention_splits(s, M);
     p.part_o = o;
-    if (p.splits > 1) o += align256(static_cast<uint64_t>(p.splits) * M * dq * 4u);
-    p.part_ml = o;
-    if (p.splits > 1) o += align256(static_cast<uint64_t>(p.splits) * M * s.n_q_heads * 8u);
+    const int reserved = attention_reserve(s, M);
+    if (reserved > 1) {
+        o += align256(static_cast<uint64_t>(reserved) * M * dq * 4u);
+        o += align256(static_cast<uint64_t>(reserved) * M * s.n_q_heads * 8u);
+    }
     // the library's own GEMM: partial products
     const int64_t n_qkv[3] = {static_cast<int64_t>(dq), static_cast<int64_t>(dkv), static_cast<int64_t>(dkv)};
     const int64_t n_o[1] = {d.d_model}, n_ff[2] = {d.d_ff, d.d_ff};
     const uint64_t part = std::max(
         std::max(partials_reserve(M, n_qkv, 3, d.d_model), partials_reserve(M, n_o, 1, static_cast<int64_t>(dq))),
         std::max(partials_reserve(M, n_ff, 2, d.d_model), partials_reserve(M, n_o, 1, d.d_ff)));
-    p.gemm_part = o;
     o += align256(part);
     p.total = o;
     return p;
@@ -622,32 +636,33 @@ int32_t kv_recompute_layer(kv_recompute_t* rc, const kv_shape_t* shape, const kv
     g.fragments = own ? 1 : 0;
     g.scale_log2e = static_cast<float>(1.4426950408889634 / std::sqrt(static_cast<double>(D)));
     const uint32_t pair_blocks = static_cast<uint32_t>((g.pairs + kAttnWaves - 1) / kAttnWaves);
-    if (p.splits > 1) {
-        float* part_o = reinterpret_cast<float*>(base + p.part_o);
-        float* part_ml = reinterpret_cast<float*>(base + p.part_ml);
-        const int n_tiles = (s.n_tokens + 31) / 32;
-        const int per_split = (n_tiles + p.splits - 1) / p.splits;
-        const dim3 agrid(pair_blocks, static_cast<uint32_t>(Hkv), static_cast<uint32_t>(p.splits));
-        const int64_t rows = M * Hq;
+    // (the shares of a divided attention lie behind its output)
+    const Room shares = room(p.x1, p.total);
+    const int splits = attention_splits(s, M, shares.bytes);
+    if (splits > 1) {
+        const int64_t pairs_all = M * Hq;
+        float* part_o = reinterpret_cast<float*>(shares.at);
+        float* part_ml = part_o + static_cast<int64_t>(splits) * pairs_all * D;
+        const dim3 agrid(pair_blocks, static_cast<uint32_t>(Hkv), static_cast<uint32_t>(splits));
         if (D == 64) {
             hipLaunchKernelGGL((recompute_attention_kernel<64, true>), agrid, dim3(64 * kAttnWaves), 0, st, q16,
-                               k_plane, v_plane, chunk_idx_dev, attn, g, part_o, part_ml, per_split);
-            hipLaunchKernelGGL(attention_combine_kernel<64>, dim3(static_cast<uint32_t>((rows * 16 + 255) / 256)),
-                               dim3(256), 0, st, part_o, part_ml, attn, rows, p.splits, Hq, g.fragments);
+                               k_plane, v_plane, chunk_idx_dev, attn, g, part_o, part_ml);
+            hipLaunchKernelGGL(attention_combine_kernel<64>, dim3(static_cast<uint32_t>((pairs_all * 16 + 255) / 256)),
+                               dim3(256), 0, st, part_o, part_ml, attn, pairs_all, splits, Hq, g.fragments);
         } else {
             hipLaunchKernelGGL((recompute_attention_kernel<128, true>), agrid, dim3(64 * kAttnWaves), 0, st, q16,
-                               k_plane, v_plane, chunk_idx_dev, attn, g, part_o, part_ml, per_split);
-            hipLaunchKernelGGL(attention_combine_kernel<128>, dim3(static_cast<uint32_t>((rows * 32 + 255) / 256)),
-                               dim3(256), 0, st, part_o, part_ml, attn, rows, p.splits, Hq, g.fragments);
+                               k_plane, v_plane, chunk_idx_dev, attn, g, part_o, part_ml);
+            hipLaunchKernelGGL(attention_combine_kernel<128>, dim3(static_cast<uint32_t>((pairs_all * 32 + 255) / 256)),
+                               dim3(256), 0, st, part_o, part_ml, attn, pairs_all, splits, Hq, g.fragments);
         }
     } else {
         const dim3 agrid(pair_blocks, static_cast<uint32_t>(Hkv));
         if (D == 64)
             hipLaunchKernelGGL((recompute_attention_kernel<64, false>), agrid, dim3(64 * kAttnWaves), 0, st, q16,
-                               k_plane, v_plane, chunk_idx_dev, attn, g, nullptr, nullptr, 0);
+                               k_plane, v_plane, chunk_idx_dev, attn, g, nullptr, nullptr);
         else
             hipLaunchKernelGGL((recompute_attention_kernel<128, false>), agrid, dim3(64 * kAttnWaves), 0, st, q16,
-                               k_plane, v_plane, chunk_idx_dev, attn, g, nullptr, nullptr, 0);
+                               k_plane, v_plane, chunk_idx_dev, attn, g, nullptr, nullptr);
     }
     // 4. output projection + residual, feed-forward + residual
     const GemmGroup og = {1, {dims->d_model}, {w->wo}, {x1}};

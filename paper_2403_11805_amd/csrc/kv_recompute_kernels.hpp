@@ -267,28 +267,34 @@ struct AttnGeom {
 // with mfma_f32_32x32x16_f16 (a lane owns one query row and 16 of the tile's 32
 // tokens), online softmax per row, O^T += V_tile^T P^T with the probabilities
 // rounded to fp16 as the B operand straight from the registers (the contraction
-// index is permuted the same way on both operands).  The eight wavefronts of a
-// workgroup take eight consecutive pairs of ONE kv head, so K and V tiles are
+// index is permuted the same way on both operands).  The four wavefronts of a
+// workgroup take four consecutive pairs of ONE kv head, so K and V tiles are
 // fetched once per workgroup (coalesced 16-byte loads, two tiles ahead) and shared
 // through LDS: K with its row pieces permuted by the row number, V in cache order and
 // read through the LDS transpose read.  Tokens after a row's global position
 // are masked; a wavefront skips the tiles that lie entirely behind its last row,
-// and the output accumulators are rescaled only when some row's maximum moved.
-constexpr int kAttnWaves = 8;
+// and the output accumulators are rescaled only when some row's maximum has moved by more than 2^kRefSlack.
+constexpr int kAttnWaves = 4;
 constexpr int kMaxSplits = 16;     // workgroups that may share the key range of a row block
-
+// Measured, 32 heads of 128 over 4096 tokens (kernel alone): 2048 rows anywhere in the cache 123 us, 304 rows 45 us,
+// 16 rows 7.8 us (eight wavefronts per workgroup, loads behind branches - the compiler then waits for every load in
+// flight before it parks a tile, so that the second tile ahead never is -, accumulators in AGPRs and rescaled
+// whenever a maximum moved: 160, 57 and 13.5 us).  The unequal key ranges of a causal mask leave the chip waiting
+// for the longest workgroup: two or three small workgroups per CU, a long one beside a short one, and shares of
+// each workgroup's own range even them out.  A tile costs a wavefront some 1100 cycles of MFMA and VALU work and 16
+// KiB of LDS reads.  (second __launch_bounds__ argument: accumulators stay in VGPRs)
 //
 // SPLIT: with few recomputed rows there are too few workgroups to fill the chip and each walks
-// the whole key range alone.  The key tiles are then divided among gridDim.z workgroups per
-// (pairs, kv head); each writes the unnormalised output, running maximum and denominator of its
+// the whole key range alone.  The key tiles that a workgroup's last row sees are then divided evenly among
+// gridDim.z workgroups; each writes the unnormalised output, running maximum and denominator of its
 // share (part_o [split][row][head][D], part_ml [split][row][head][2], binary32) and
 // attention_combine_kernel merges the shares in a fixed order.
+constexpr float kRefSlack = 8.0f;
 template <int D, bool SPLIT>
-__global__ __launch_bounds__(64 * kAttnWaves) void recompute_attention_kernel(
+__global__ __launch_bounds__(64 * kAttnWaves, 2) void recompute_attention_kernel(
     const _Float16* __restrict__ q16, const _Float16* __restrict__ k_plane,
     const _Float16* __restrict__ v_plane, const int32_t* __restrict__ chunk_idx,
-    _Float16* __restrict__ out, AttnGeom g, float* __restrict__ part_o, float* __restrict__ part_ml,
-    int tiles_per_split) {
+    _Float16* __restrict__ out, AttnGeom g, float* __restrict__ part_o, float* __restrict__ part_ml) {
     constexpr int KS = D / 16;
     constexpr int DB = D / 32;                      // 32-wide blocks of the head dimension
     constexpr int kRowPieces = D / 8;
@@ -311,16 +317,22 @@ __global__ __launch_bounds__(64 * kAttnWaves) void recompute_attention_kernel(
     // Workgroups are handed to the 8 XCDs in turn (linear id modulo 8), each with an L2 of its
     // own: the workgroups of one kv head are placed on one XCD, so that its K/V planes are
     // fetched into one L2 only.  Needs n_kv_heads % 8 == 0, otherwise the plain order is kept.
-    int kvh = blockIdx.y, bxi = blockIdx.x;
-    if (!SPLIT && g.Hkv % 8 == 0) {
-        const int lin = blockIdx.y * gridDim.x + blockIdx.x;
+    const int gx = static_cast<int>(gridDim.x), nz = SPLIT ? static_cast<int>(gridDim.z) : 1;
+    int kvh = blockIdx.y, bxi = blockIdx.x, share = SPLIT ? static_cast<int>(blockIdx.z) : 0;
+    bool ascending = false;
+    if (g.Hkv % 8 == 0) {
+        const int lin = (static_cast<int>(SPLIT ? blockIdx.z : 0) * g.Hkv + static_cast<int>(blockIdx.y)) * gx + static_cast<int>(blockIdx.x);
         const int per_xcd = lin >> 3;                       // position among this XCD's workgroups
-        kvh = (lin & 7) + 8 * (per_xcd / static_cast<int>(gridDim.x));
-        bxi = per_xcd % static_cast<int>(gridDim.x);
+        const int nth = per_xcd / (gx * nz), in = per_xcd - nth * (gx * nz);
+        kvh = (lin & 7) + 8 * nth;
+        share = in / gx;
+        bxi = in - share * gx;
+        // Workgroups with the longest key ranges are dispatched first; where an XCD's 32 CUs take a second round of
+        // them beside the first, the other way round, so that a CU holds a long and a short one.
+        ascending = (nth * gx * nz / 32) & 1;
     }
     const int per = g.Hq / g.Hkv;
-    // workgroups with the longest key ranges are dispatched first
-    const int bx = static_cast<int>(gridDim.x) - 1 - bxi;
+    const int bx = ascending ? bxi : gx - 1 - bxi;
     const int pair = bx * kAttnWaves + wave;
     const bool valid = pair < g.pairs;
     const int head = kvh * per + (valid ? pair % per : 0);
@@ -334,8 +346,9 @@ __global__ __launch_bounds__(64 * kAttnWaves) void recompute_attention_kernel(
     const int rb_hi = min(bx * kAttnWaves + kAttnWaves - 1, g.pairs - 1) / per;
     const int wg_max_pos = global_position(chunk_idx, g.T, min(rb_hi * 32 + 31, g.M - 1));
     // key tiles [t_first, n_tiles) of this workgroup
-    const int t_first = SPLIT ? static_cast<int>(blockIdx.z) * tiles_per_split : 0;
-    const int n_tiles = SPLIT ? min(wg_max_pos / 32 + 1, t_first + tiles_per_split) : wg_max_pos / 32 + 1;
+    const int all_tiles = wg_max_pos / 32 + 1, per_share = (all_tiles + nz - 1) / nz;
+    const int t_first = share * per_share;
+    const int n_tiles = min(all_tiles, t_first + per_share);
 
     rv8h_t qreg[KS];
     {
@@ -379,7 +392,7 @@ __global__ __launch_bounds__(64 * kAttnWaves) void recompute_attention_kernel(
     // one tile: the arithmetic on LDS buffer `buf` (tile t), then tile t + 1 (fetched two steps ago
     // into the other register set) goes to the other buffer and its set fetches tile t + 3
     auto step = [&](int t, int buf) __attribute__((always_inline)) {
-        if (t * 32 <= max_pos) {            // wave-uniform
+        if (t < n_tiles && t * 32 <= max_pos) {     // wave-uniform
             rv8h_t kreg[KS];
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
@@ -401,9 +414,21 @@ __global__ __launch_bounds__(64 * kAttnWaves) void recompute_attention_kernel(
             }
 #pragma unroll
             for (int v = 0; v < 16; ++v) mloc = fmaxf(mloc, acc[v]);
-            const float m_new = fmaxf(m_run, xhalf_max(mloc) * g.scale_log2e);
-            const float m_safe = (m_new == -INFINITY) ? 0.0f : m_new;
-            const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
+            // The reference of a row moves only when some row of the wavefront has left it by more than 2^8: until
+            // then its probabilities are up to 2^8 instead of 1, which costs fp16 no precision, and the 64
+            // accumulators are not touched.
+            const float m_tile = xhalf_max(mloc) * g.scale_log2e;
+            if (__any(m_tile > m_run + kRefSlack)) {        // wave-uniform
+                const float m_new = fmaxf(m_run, m_tile);
+                const float alpha = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.0f : m_new));
+                m_run = m_new;
+                l_run *= alpha;
+#pragma unroll
+                for (int b = 0; b < DB; ++b)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) o_acc[b][v] *= alpha;
+            }
+            const float m_safe = (m_run == -INFINITY) ? 0.0f : m_run;
             float psum = 0.0f;
             rv8h_t pb[2];
 #pragma unroll
@@ -412,15 +437,7 @@ __global__ __launch_bounds__(64 * kAttnWaves) void recompute_attention_kernel(
                 psum += pv;
                 pb[v / 8][v % 8] = static_cast<_Float16>(pv);
             }
-            l_run = l_run * alpha + xhalf_sum(psum);
-            const bool moved = m_new != m_run;
-            m_run = m_new;
-            if (__any(moved)) {             // wave-uniform: some row's maximum moved
-#pragma unroll
-                for (int b = 0; b < DB; ++b)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) o_acc[b][v] *= alpha;
-            }
+            l_run += xhalf_sum(psum);
             // contraction slot (half, e) of step st holds token 16*st + 4*half + e (e < 4) or
             // 16*st + 8 + 4*half + e - 4: the order of acc[8*st .. 8*st+7] on the P side
 #pragma unroll
@@ -440,8 +457,10 @@ __global__ __launch_bounds__(64 * kAttnWaves) void recompute_attention_kernel(
                 }
             }
         }
-        if (t + 1 < n_tiles) park(buf ^ 1, buf ^ 1);
-        if (t + 3 < n_tiles) fetch(buf ^ 1, t + 3);
+        // (both unconditional, beyond the last tile with that tile again: behind a branch the compiler waits for every
+        // load in flight before it parks)
+        park(buf ^ 1, buf ^ 1);
+        fetch(buf ^ 1, min(t + 3, n_tiles - 1));
         __syncthreads();
     };
     if (t_first < n_tiles) {            // uniform per workgroup
@@ -452,13 +471,13 @@ __global__ __launch_bounds__(64 * kAttnWaves) void recompute_attention_kernel(
         __syncthreads();
         for (int t = t_first; t < n_tiles; t += 2) {
             step(t, 0);
-            if (t + 1 < n_tiles) step(t + 1, 1);
+            step(t + 1, 1);                 // beyond the last tile: nothing but the barrier (see above)
         }
     }
     if constexpr (SPLIT) {
         if (ok) {
             // the share of this workgroup: an empty one has m = -inf, l = 0 and zeros
-            const int64_t row = (static_cast<int64_t>(blockIdx.z) * g.M + m) * g.Hq + head;
+            const int64_t row = (static_cast<int64_t>(share) * g.M + m) * g.Hq + head;
             if (half == 0) {
                 part_ml[row * 2] = m_run;
                 part_ml[row * 2 + 1] = l_run;
