@@ -53,7 +53,7 @@ __host__ __device__ __forceinline__ int64_t fragment_at(int m, int k, int M, int
 struct GemmArgs {
     const _Float16* A;                  // [M][K] in fragment order
     const _Float16* B[kGemmMaxMats];    // [K][N[j]]
-    void* C[kGemmMaxMats];              // [M][N[j]] fp16 or binary32, row-major or (fp16 only) in fragment order
+    void* C[kGemmMaxMats];              // [M][N[j]] fp16 or binary32, row-major or (fp16, gemm_stream_kernel) in fragment order
     const _Float16* Cin;                // [M][N[0]] fp16 or NULL (added before the result is rounded; one matrix only)
     float* part;                        // matrix j: part + part_at[j], [splits][M][N[j]] binary32 (splits > 1)
     uint64_t part_at[kGemmMaxMats];
@@ -241,7 +241,9 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs g) {
 // At few rows a step is bound by its chain of waits (no MFMAs at all: 81 of 92 us for gate | up at 304 rows), at
 // many by the chip's power and by the last round of workgroups.
 // Grid (8 * ceil(column tiles / 8) * row tiles, splits), 256 threads; kGemmStage divides g.steps.
-template <int MB>
+// GATED: two matrices of one width, splits == 1, and the result is C[0] = fp16(silu(A B[0]) * (A B[1])) in fragment
+// order, both products rounded to fp16 first; a column tile is 128 columns of each.
+template <int MB, bool GATED>
 __global__ __launch_bounds__(256, MB <= 4 ? 2 : 1) void gemm_tile_kernel(GemmArgs g) {
     constexpr int kSets = MB <= 4 ? 4 : 8;           // steps of weights in registers
     constexpr int kUnroll = kSets / kGemmStage;      // stages per trip, so that the sets are named statically
@@ -256,8 +258,10 @@ __global__ __launch_bounds__(256, MB <= 4 ? 2 : 1) void gemm_tile_kernel(GemmArg
     const int grp = blockIdx.x / (8 * row_tiles), local = blockIdx.x - grp * 8 * row_tiles;
     const int tile = grp * 8 + (local & 7), m0 = (local >> 3) * MB * 32;
     if (tile >= g.tile_end[kGemmMaxMats - 1]) return;
-    const int mat = (tile >= g.tile_end[0]) + (tile >= g.tile_end[1]);
-    const int n0 = (tile - (mat ? g.tile_end[mat - 1] : 0)) * kTileCols + wave * 64;
+    // GATED: wavefronts 0 and 1 hold 128 columns of matrix 0, 2 and 3 the same columns of matrix 1
+    const int mat = GATED ? wave >> 1 : (tile >= g.tile_end[0]) + (tile >= g.tile_end[1]);
+    const int n0 = GATED ? tile * (kTileCols / 2) + (wave & 1) * 64
+                           : (tile - (mat ? g.tile_end[mat - 1] : 0)) * kTileCols + wave * 64;
     const int N = g.N[mat], K = g.K, K8 = K / 8;
     const int s_all = (K + kGemmStep - 1) / kGemmStep;
     const int sb = blockIdx.y * g.steps, se = min(s_all, sb + g.steps);
@@ -400,30 +404,77 @@ __global__ __launch_bounds__(256, MB <= 4 ? 2 : 1) void gemm_tile_kernel(GemmArg
     for (int u = 0; u < kUnroll; ++u)
         if (s + u < n_stages) run_stage(s + u, u, std::true_type{});
     // acc[c][b][v]: row m0 + b*32 + 8*(v/4) + 4*half + v%4, column n0 + 2*j + c.  Through LDS, block by block and
-    // each wavefront for itself, so that the results leave in 16-byte pieces of either layout (rows padded by four
-    // floats: the pieces of 16 rows fall on different banks)
+    // each wavefront for itself, so that the results leave in 16-byte pieces (rows padded by four floats)
     constexpr int kPitch = 64 + 4;
     static_assert(4 * 32 * kPitch * 4 <= 3 * kBuf * 16, "the staging buffers hold a block per wavefront");
     __syncthreads();
     float* tile_lds = reinterpret_cast<float*>(stage_lds) + wave * 32 * kPitch;
+    if constexpr (GATED) {
+        // Two row blocks at a time: the wavefront of matrix 0 finishes the first, its partner with the same columns
+        // of matrix 1 the second; each hands the other the block it needs, lane by lane.
+        const bool second = wave >= 2;
+        const float* theirs = reinterpret_cast<float*>(stage_lds) + (wave ^ 2) * 32 * kPitch;
+        _Float16* act_lds = reinterpret_cast<_Float16*>(tile_lds);
+        constexpr int kActPitch = 64 + 8;            // halves
 #pragma unroll
-    for (int b = 0; b < MB; ++b) {
+        for (int b = 0; b < MB; b += 2) {
+            const int b2 = b + 1 < MB ? b + 1 : b;
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
-            *reinterpret_cast<gv2f_t*>(tile_lds + (8 * (v / 4) + 4 * half + v % 4) * kPitch + 2 * j) = gv2f_t{acc[0][b][v], acc[1][b][v]};
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            for (int v = 0; v < 16; ++v)
+                *reinterpret_cast<gv2f_t*>(tile_lds + (v * 64 + lane) * 2) =
+                    second ? gv2f_t{acc[0][b][v], acc[1][b][v]} : gv2f_t{acc[0][b2][v], acc[1][b2][v]};
+            __syncthreads();
+            gv2f_t other[16];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = g.out_fragments ? j : 8 * i + (lane >> 3), c8 = g.out_fragments ? 2 * i + half : lane & 7;
-            const gv4f_t* src = reinterpret_cast<const gv4f_t*>(tile_lds + r * kPitch + 8 * c8);
-            const int m = m0 + b * 32 + r, n = n0 + 8 * c8;
-            if (m < g.M && n < N) gemm_store8(g, mat, m, n, src[0], src[1]);
+            for (int v = 0; v < 16; ++v) other[v] = *reinterpret_cast<const gv2f_t*>(theirs + (v * 64 + lane) * 2);
+            __syncthreads();
+            const int mb = m0 + (second ? b2 : b) * 32;
+            if (second && b2 == b) continue;         // (uniform; nothing is left of an odd number of blocks)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                gv2h_t o;
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const float own = second ? acc[c][b2][v] : acc[c][b][v];
+                    const float x = static_cast<float>(static_cast<_Float16>(second ? other[v][c] : own));
+                    const float u = static_cast<float>(static_cast<_Float16>(second ? own : other[v][c]));
+                    o[c] = static_cast<_Float16>(x / (1.0f + __expf(-x)) * u);
+                }
+                *reinterpret_cast<gv2h_t*>(act_lds + (8 * (v / 4) + 4 * half + v % 4) * kActPitch + 2 * j) = o;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int c8 = 2 * i + half, m = mb + j, n = n0 + 8 * c8;
+                const gv8h_t r = *reinterpret_cast<const gv8h_t*>(act_lds + j * kActPitch + 8 * c8);
+                if (m < g.M && n < N) *reinterpret_cast<gv8h_t*>(static_cast<_Float16*>(g.C[0]) + fragment_at(m, n, g.M, N)) = r;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+#pragma unroll
+        for (int b = 0; b < MB; ++b) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                *reinterpret_cast<gv2f_t*>(tile_lds + (8 * (v / 4) + 4 * half + v % 4) * kPitch + 2 * j) = gv2f_t{acc[0][b][v], acc[1][b][v]};
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int r = 8 * i + (lane >> 3), c8 = lane & 7;
+                const gv4f_t* src = reinterpret_cast<const gv4f_t*>(tile_lds + r * kPitch + 8 * c8);
+                const int m = m0 + b * 32 + r, n = n0 + 8 * c8;
+                if (m < g.M && n < N) gemm_store8(g, mat, m, n, src[0], src[1]);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
     }
 }
 

@@ -44,11 +44,11 @@ typedef int (*rb_get_solutions_fn)(rb_handle, int, int, int, int, int, const voi
                                    const void*, int, int, const void*, const void*, int, int, void*, int, int,
                                    int, int, uint32_t, int*, int*);
 
-// Measured on MI355X, a whole layer in us: own kernels / the GEMM library's standard choice above
-//   d_model 4096, 32 kv heads, d_ff 11008:  1024 rows 635 / 644   1536 rows 880 / 868   2048 rows 1091 / 1263
-//   d_model 4096,  8 kv heads, d_ff 14336:  2048 rows 1135 / 1093
-// (the library's choice varies with the shape; below, the own kernels are ahead everywhere: 512 rows 366, 348 us of
-// projections alone before them)
+// Measured on MI355X, a whole layer in us: own kernels / the GEMM library's standard choice
+//   d_model 4096, 32 kv heads, d_ff 11008:  1536 rows 808 / 852   2048 rows 982 / 1208   2560 rows 1203 / 1167
+//                                           3072 rows 1403 / 1476   4096 rows 1844 / 1839
+//   d_model 4096,  8 kv heads, d_ff 14336:  2048 rows 1024 / 1070
+//   d_model 2048, 16 kv heads, d_ff 5632:   1024 rows 236 / 302   2048 rows 413 / 432
 constexpr int64_t kOwnGemmRows = KV_RECOMPUTE_OWN_GEMM_ROWS;
 
 uint64_t align256(uint64_t v) { return (v + 255) & ~static_cast<uint64_t>(255); }
@@ -268,12 +268,16 @@ Room larger(Room a, Room b) { return a.bytes >= b.bytes ? a : b; }
 
 // What became of a group's product: complete in the C matrices (splits == 1), or `splits` partial products per
 // matrix, matrix after matrix ([splits][M][N[j]] binary32), from `part` on, for the caller's next kernel to add.
+// gated: C[0] already holds silu(first) * second.
 struct Product {
     int splits;
     const float* part;
+    bool gated;
 };
 
-enum class Out { kF32, kF16, kF16Fragments };
+// kGate: two matrices of one width for a gated activation, in fragment order; where the kernel at hand can, it
+// applies the activation itself (a layer of 2048 rows: 23 us of silu_mul_kernel and the way through memory).
+enum class Out { kF32, kF16, kGate };
 
 // The library's own GEMM (kv_gemm_kernels.hpp) over a group of weight matrices; A in fragment order.  Without
 // `left` (one matrix only) a divided product is added here.
@@ -284,7 +288,9 @@ int own_gemm(hipStream_t st, int64_t M, int64_t K, const void* A, const GemmGrou
         return fail(KV_ESHAPE, "GEMM (%s): unsupported shape", what);
     for (int j = 0; j < grp.n; ++j)
         if (grp.N[j] % 8 || grp.N[j] < 8) return fail(KV_ESHAPE, "GEMM (%s) needs N a multiple of 8", what);
-    const OwnGemm h = own_gemm_plan(M, grp.N, grp.n, K, room.bytes);
+    OwnGemm h = own_gemm_plan(M, grp.N, grp.n, K, room.bytes);
+    const bool gated = out == Out::kGate && !h.stream && h.splits == 1;
+    if (gated) h.col_tiles = static_cast<uint32_t>((grp.N[0] + kTileCols / 2 - 1) / (kTileCols / 2));
     const int64_t cols = h.stream ? kStreamCols : kTileCols;
     GemmArgs g;
     g.A = static_cast<const _Float16*>(A);
@@ -304,12 +310,13 @@ int own_gemm(hipStream_t st, int64_t M, int64_t K, const void* A, const GemmGrou
         }
         g.tile_end[j] = tiles;
     }
+    if (gated) g.tile_end[0] = g.tile_end[1] = g.tile_end[2] = static_cast<int32_t>(h.col_tiles);
     g.M = static_cast<int32_t>(M);
     g.K = static_cast<int32_t>(K);
     g.steps = h.steps;
     g.splits = h.splits;
     g.out_f32 = out == Out::kF32 ? 1 : 0;
-    g.out_fragments = out == Out::kF16Fragments ? 1 : 0;
+    g.out_fragments = out == Out::kGate && h.splits == 1 ? 1 : 0;
     if (h.stream) {
         const dim3 grid(h.col_tiles, static_cast<uint32_t>(h.splits), h.row_tiles);
         if (h.mb == 1) hipLaunchKernelGGL(gemm_stream_kernel<1>, grid, dim3(256), 0, st, g);
@@ -318,16 +325,22 @@ int own_gemm(hipStream_t st, int64_t M, int64_t K, const void* A, const GemmGrou
         const int64_t blocks = static_cast<int64_t>((h.col_tiles + 7) / 8 * 8) * h.row_tiles;
         if (blocks > 0x7fffffffLL) return fail(KV_ESHAPE, "GEMM (%s): grid exceeds 2^31 workgroups", what);
         const dim3 grid(static_cast<uint32_t>(blocks), static_cast<uint32_t>(h.splits));
+#define KV_TILE(MB)                                                                                       \
+    do {                                                                                                  \
+        if (gated) hipLaunchKernelGGL((gemm_tile_kernel<MB, true>), grid, dim3(256), 0, st, g);           \
+        else hipLaunchKernelGGL((gemm_tile_kernel<MB, false>), grid, dim3(256), 0, st, g);                \
+    } while (0)
         switch (h.mb) {
-            case 3: hipLaunchKernelGGL(gemm_tile_kernel<3>, grid, dim3(256), 0, st, g); break;
-            case 4: hipLaunchKernelGGL(gemm_tile_kernel<4>, grid, dim3(256), 0, st, g); break;
-            case 5: hipLaunchKernelGGL(gemm_tile_kernel<5>, grid, dim3(256), 0, st, g); break;
-            case 6: hipLaunchKernelGGL(gemm_tile_kernel<6>, grid, dim3(256), 0, st, g); break;
-            case 7: hipLaunchKernelGGL(gemm_tile_kernel<7>, grid, dim3(256), 0, st, g); break;
-            default: hipLaunchKernelGGL(gemm_tile_kernel<8>, grid, dim3(256), 0, st, g); break;
+            case 3: KV_TILE(3); break;
+            case 4: KV_TILE(4); break;
+            case 5: KV_TILE(5); break;
+            case 6: KV_TILE(6); break;
+            case 7: KV_TILE(7); break;
+            default: KV_TILE(8); break;
         }
+#undef KV_TILE
     }
-    if (left) *left = {h.splits, reinterpret_cast<const float*>(room.at)};
+    if (left) *left = {h.splits, reinterpret_cast<const float*>(room.at), gated};
     else if (h.splits > 1)
         hipLaunchKernelGGL(gemm_reduce_kernel, dim3(static_cast<uint32_t>((M * grp.N[0] / 4 + 255) / 256)), dim3(256), 0, st, g);
     hipError_t e = hipGetLastError();
@@ -343,7 +356,7 @@ bool own_projections(const kv_recompute* rc, int64_t M) { return M <= kOwnGemmRo
 int gemm(kv_recompute* rc, hipStream_t stream, int64_t M, int64_t K, const void* A, const GemmGroup& grp, const void* Cin,
          Out out, Room room, Product* left, const char* what) {
     if (own_projections(rc, M)) return own_gemm(stream, M, K, A, grp, Cin, out, room, left, what);
-    if (left) *left = {1, nullptr};
+    if (left) *left = {1, nullptr, false};
     for (int j = 0; j < grp.n; ++j) {
         const GemmShape g = {M, grp.N[j], K, out == Out::kF32, Cin != nullptr};
         int solution = -1;
@@ -676,11 +689,11 @@ int32_t kv_recompute_layer(kv_recompute_t* rc, const kv_shape_t* shape, const kv
         hipLaunchKernelGGL((rmsnorm_kernel<false, false>), rows, dim3(256), 0, st, nullptr, 1, x1, nullptr, norm2, xn, m32, dims->d_model, dims->rms_eps);
     const GemmGroup ff = {2, {dims->d_ff, dims->d_ff}, {w->w_gate, w->w_up}, {gate, up}};
     // (the activation goes to `gate`)
-    if (int e = gemm(rc, st, M, dims->d_model, xn, ff, nullptr, own ? Out::kF16Fragments : Out::kF16,
+    if (int e = gemm(rc, st, M, dims->d_model, xn, ff, nullptr, own ? Out::kGate : Out::kF16,
                      larger(room(p.q32, p.x1), room(p.part_o, p.total)), &pr, "gate | up")) return e;
     const int64_t n8 = M * (dims->d_ff / 8);
     const float* no_part = nullptr;
-    hipLaunchKernelGGL(silu_mul_kernel, dim3(static_cast<uint32_t>((n8 + 255) / 256)), dim3(256), 0, st, gate, up,
+    if (!pr.gated) hipLaunchKernelGGL(silu_mul_kernel, dim3(static_cast<uint32_t>((n8 + 255) / 256)), dim3(256), 0, st, gate, up,
                        gate, m32, dims->d_ff, pr.splits > 1 ? pr.part : no_part,
                        pr.splits > 1 ? pr.part + pr.splits * M * dims->d_ff : no_part, pr.splits, own ? 1 : 0);
     const GemmGroup down = {1, {dims->d_model}, {w->w_down}, {x_out}};

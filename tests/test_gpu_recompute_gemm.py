@@ -21,7 +21,9 @@ def some(n, of, seed):
     (1, 2, 2, 64, 256, 8, 1000, 520, 0, some(9, 32, 1)),         # 72 rows: tiled, three row blocks; K = 1000 divided
     (1, 1, 2, 64, 256, 8, 520, 1000, 0, some(13, 32, 2)),        # 104 rows: four row blocks, the last of 8
     (1, 1, 2, 128, 512, 16, 264, 712, 0, some(17, 32, 3)),       # 272 rows: two row tiles, the last block of 16
-    (1, 2, 4, 64, 1024, 16, 136, 1032, 0, some(46, 64, 4)),      # 736 rows
+    (1, 2, 4, 64, 1024, 16, 136, 1032, 0, some(46, 64, 4)),      # 736 rows; too short a K to divide: gate and up gated in one
+    (1, 1, 2, 64, 512, 8, 56, 136, 0, some(29, 64, 5)),          # 232 rows, gated: an odd number of row blocks, the last of 8
+    (1, 1, 1, 64, 256, 8, 64, 8, 0, some(12, 32, 6)),            # 96 rows, gated: one piece of columns
 ])
 def test_projection_edges(case):
     run_case(*case, seed=71)
