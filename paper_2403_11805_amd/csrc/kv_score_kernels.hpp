@@ -302,47 +302,6 @@ __global__ __launch_bounds__(256) void score_tiles_kernel(const _Float16* __rest
     }
 }
 
-// Partials of a tile whose entries are all visible, against the row's current
-// reference, with no branch and no maximum pass: straight-line code that can be
-// interleaved with the MFMAs of the next tile.  Both halves of the wavefront
-// store the same values to the same slots; padding rows have slots of their own
-// (rows_p per tile).  `bad` collects rows whose sum left the safe range: the
-// caller then redoes the tile through tile_epilogue.
-//   SBT = sub-blocks per tile (32 / sb_tokens); es = this lane's slots of the tile.  The reference is
-//   the same for every tile of the pass and is stored once per run by the caller (ScoreWs::m_fast).
-template <int SBT>
-__device__ __forceinline__ void fast_epilogue(const v16f_t& acc, float scale_log2e, float w,
-                                              float m_ref, float& l_run, uint32_t& bad,
-                                              float* __restrict__ es, int rows_p) {
-    float l4[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        float a = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[4 * k], scale_log2e, -m_ref));
-#pragma unroll
-        for (int i = 1; i < 4; ++i)
-            a += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[4 * k + i], scale_log2e, -m_ref));
-        l4[k] = a;
-    }
-    float sub[SBT];
-    float lsum;
-    if constexpr (SBT == 1) {
-        sub[0] = xhalf_sum((l4[0] + l4[1]) + (l4[2] + l4[3]));
-        lsum = sub[0];
-    } else if constexpr (SBT == 2) {
-        sub[0] = xhalf_sum(l4[0] + l4[1]);
-        sub[1] = xhalf_sum(l4[2] + l4[3]);
-        lsum = sub[0] + sub[1];
-    } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) sub[k] = xhalf_sum(l4[k]);
-        lsum = (sub[0] + sub[1]) + (sub[2] + sub[3]);
-    }
-    l_run += lsum;
-    bad |= (lsum < kRefOverflow) ? 0u : 1u;
-#pragma unroll
-    for (int k = 0; k < SBT; ++k) es[k * rows_p] = sub[k] * w;
-}
-
 // Variant for grouped-query attention: the 2-4 wavefronts of a workgroup hold
 // the row blocks (shared_blocks_per_wave each) of different query heads that read the SAME kv head,
 // so K is fetched once per workgroup (fully coalesced, 16 bytes per thread and
@@ -353,10 +312,15 @@ __device__ __forceinline__ void fast_epilogue(const v16f_t& acc, float scale_log
 // A run is processed in up to three passes over its tiles:
 //  - the fast pass over the tiles below the causal diagonal.  The row references
 //    come from the run's first tile; the loads of a stage are issued two stages
-//    ahead (two register sets used in turn), and inside a wavefront the MFMAs of
-//    a tile are interleaved, instruction by instruction, with the softmax
-//    partials (fast_epilogue) of the tile before it (two accumulator sets used in
-//    turn), so that the matrix pipe and the VALU work overlap;
+//    ahead (two register sets used in turn), operands are read from LDS a tile
+//    ahead, into the register the tile at hand has just used, and inside a
+//    wavefront the MFMAs of a tile are interleaved, instruction by instruction,
+//    with the softmax partials of the tile before it (two accumulator sets used in
+//    turn).  Bound by those partials: per block of 32 x 32 some 52 VALU
+//    instructions and 16 exponentials at a quarter of their rate, 420 cycles
+//    against 256 of MFMA (32 layers x 32 heads on 8 kv heads, 32768 tokens, R = 64:
+//    751 us per call; 797 with the order left to sched_group_barrier patterns and
+//    the loads behind branches, where the compiler drains them);
 //  - the general pass (tile_epilogue) over the tiles that reach the diagonal;
 //  - the general pass over the whole fast range again if some sum left the safe
 //    range there (workgroup-wide decision), or instead of the fast pass if a
@@ -403,7 +367,6 @@ __global__ __launch_bounds__(256, 2) void score_tiles_shared_kernel(const _Float
     v8h_t qreg[NRBW][KS];
     int row[NRBW], lh[NRBW];
     float m_run[NRBW], l_run[NRBW];
-    float* es_base[NRBW];     // this lane's slot of tile 0 in e_sub
 #pragma unroll
     for (int u = 0; u < NRBW; ++u) {
         const int rb = rg * NRBW + u;
@@ -415,7 +378,6 @@ __global__ __launch_bounds__(256, 2) void score_tiles_shared_kernel(const _Float
         lh[u] = l * g.Hq + head;
         m_run[u] = -INFINITY;
         l_run[u] = 0.0f;
-        es_base[u] = ws.e_sub + static_cast<int64_t>(lh[u]) * g.n_tiles * SBT * g.rows_p + r;
         const _Float16* qp = q + (static_cast<int64_t>(lh[u]) * g.R + (ok ? r : 0)) * D + half * 8;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -507,16 +469,151 @@ __global__ __launch_bounds__(256, 2) void score_tiles_shared_kernel(const _Float
     int dirty = 0;
     if (fast_end > tile_begin) {
         const float w_const = (g.norm_mode == 0) ? g.inv_R : 1.0f;
-        su4_t sa[kPerThread], sb[kPerThread];   // stages in flight: sa holds odd stages, sb even ones
-        fetch(sb, tile_begin, fast_end);
-        park(sb, 0);
-        fetch(sa, tile_begin + TS, fast_end);
+        const int n_fast = fast_end - tile_begin;
+        su4_t st[2][kPerThread];                // stages in flight: stage s of the pass in set s & 1
+        // piece i * 256 + tid of a stage; the tile is a scalar offset from the run's first (a tile has 256 pieces or a
+        // multiple), one beyond the pass is replaced by its last
+        static_assert(kTilePieces % 256 == 0, "a thread's piece i lies in one tile for all threads");
+        const __amdgpu_buffer_rsrc_t k_run = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<su4_t*>(kbase + static_cast<int64_t>(tile_begin) * kTilePieces), static_cast<short>(0), 0xffffffffu, 0x00027000);
+        auto load_piece = [&](int set, int stage, int i) __attribute__((always_inline)) {
+            const int tile = min(stage * TS + i * 256 / kTilePieces, n_fast - 1);
+            st[set][i] = __builtin_bit_cast(su4_t, __builtin_amdgcn_raw_buffer_load_b128(
+                k_run, static_cast<uint32_t>(tid) * 16u, static_cast<uint32_t>(tile * kTilePieces + i * 256 % kTilePieces) * 16u, 0));
+        };
+        auto fetch_stage = [&](int set, int stage) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < kPerThread; ++i) load_piece(set, stage, i);
+        };
+        v8h_t kreg[KS];
+        v16f_t acc[2][NRBW];                    // tile i of the pass in acc[i & 1]
+        // K operand ks of a tile from stage buffer `buf`, tile j of the stage
+        auto read_k = [&](int ks, int buf, int j) __attribute__((always_inline)) {
+            // (pieces 16 and up as a constant offset: swz < 16 leaves them where they are)
+            const int r = j * 32 + lrow;
+            kreg[ks] = __builtin_bit_cast(v8h_t, kstage[buf][r * kRowPieces + ((2 * (ks & 7) + half) ^ swz(r)) + 2 * (ks & ~7)]);
+        };
+        auto mfma = [&](int cur, int u, int ks) __attribute__((always_inline)) {
+            const v16f_t zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+            acc[cur][u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kreg[ks], qreg[u][ks], ks ? acc[cur][u] : zero, 0, 0, 0);
+        };
+        // e_sub of this wavefront's heads: stores take the tile as a scalar offset (rows_p * SBT floats per tile)
+        __amdgpu_buffer_rsrc_t es_rows[NRBW];
+        uint32_t es_lane[NRBW];
+#pragma unroll
+        for (int u = 0; u < NRBW; ++u) {
+            es_rows[u] = __builtin_amdgcn_make_buffer_rsrc(ws.e_sub + static_cast<int64_t>(lh[u]) * g.n_tiles * SBT * g.rows_p,
+                                                           static_cast<short>(0), 0xffffffffu, 0x00027000);
+            es_lane[u] = static_cast<uint32_t>(((rg * NRBW + u) % g.RB) * 32 + lrow) * 4u;
+        }
+        // Partials of block u of a tile whose exponentials are summed up in l4, against the row's current reference;
+        // both halves of the wavefront store the same values to the same slots, padding rows have slots of their own.
+        auto finish = [&](int u, const float (&l4)[4], int tile) __attribute__((always_inline)) {
+            float sub[SBT], lsum;
+            if constexpr (SBT == 1) {
+                sub[0] = xhalf_sum((l4[0] + l4[1]) + (l4[2] + l4[3]));
+                lsum = sub[0];
+            } else if constexpr (SBT == 2) {
+                sub[0] = xhalf_sum(l4[0] + l4[1]);
+                sub[1] = xhalf_sum(l4[2] + l4[3]);
+                lsum = sub[0] + sub[1];
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) sub[k] = xhalf_sum(l4[k]);
+                lsum = (sub[0] + sub[1]) + (sub[2] + sub[3]);
+            }
+            l_run[u] += lsum;
+#pragma unroll
+            for (int k = 0; k < SBT; ++k)
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, sub[k] * w_const), es_rows[u], es_lane[u],
+                                                      static_cast<uint32_t>(tile * SBT + k) * static_cast<uint32_t>(g.rows_p) * 4u, 0);
+        };
+        // The MFMAs of one tile into acc[cur], and behind each of them (the scheduling barriers fix the order) one K
+        // operand of the next tile, read into the register just used, and a share of the partials of the tile before,
+        // acc[cur ^ 1]: the FMAs of this share, the exponentials of the last, the additions of the one before that,
+        // so that no instruction waits for its neighbour.  `behind` is called once per MFMA with its number.
+        constexpr int V = 16 / KS;              // exponentials per MFMA
+        auto fast_tile = [&](int cur, int nbuf, int nj, int tile, auto&& behind) __attribute__((always_inline)) {
+            constexpr int kShares = KS * NRBW;
+            float f[2][V], ex[2][V], l4[NRBW][4];
+#pragma unroll
+            for (int i = 0; i < kShares + 2; ++i) {
+                if (i < kShares) {
+                    const int ks = i / NRBW, u = i % NRBW;
+                    mfma(cur, u, ks);
+                    if (u == NRBW - 1) read_k(ks, nbuf, nj);
+                }
+#pragma unroll
+                for (int k = 0; k < V; ++k) {
+                    if (i < kShares) {
+                        const int e = i * V + k, u = e / 16, v = e % 16;
+                        f[i & 1][k] = __builtin_fmaf(acc[cur ^ 1][u][v], g.scale_log2e, -m_run[u]);
+                    }
+                    if (i >= 1 && i <= kShares) ex[i & 1][k] = __builtin_amdgcn_exp2f(f[(i & 1) ^ 1][k]);
+                    if (i >= 2) {
+                        const int e = (i - 2) * V + k, u = e / 16, v = e % 16;
+                        const float x = ex[(i & 1) ^ 1][k];
+                        l4[u][v / 4] = v % 4 ? l4[u][v / 4] + x : x;
+                        if (v == 15) finish(u, l4[u], tile - 1);
+                    }
+                }
+                if (i < kShares) behind(i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        auto last_tile = [&](int set, int tile) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < NRBW; ++u) {
+                float l4[4];
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const float x = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[set][u][v], g.scale_log2e, -m_run[u]));
+                    l4[v / 4] = v % 4 ? l4[v / 4] + x : x;
+                }
+                finish(u, l4, tile);
+            }
+        };
+        // one piece of stage s + 1 of this pass to its buffer, its registers asked for stage s + 3 (loads are
+        // unconditional: behind a branch the compiler waits for all that are in flight)
+        auto next_stage = [&](int set, int stage, int i) __attribute__((always_inline)) {
+            const int p = i * 256 + tid, r = p / kRowPieces, c = p % kRowPieces;
+            kstage[set][r * kRowPieces + (c ^ swz(r))] = st[set][i];
+            load_piece(set, stage + 2, i);
+        };
+        auto all_next = [&](int set, int stage) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < kPerThread; ++i) next_stage(set, stage, i);
+        };
+        // Operands are read one tile ahead of the MFMAs, so a buffer is free a tile before its last MFMA.  Two tiles per
+        // stage: stage s + 1 is parked during the first tile of stage s (the last reads of its buffer were issued during
+        // the first tile of stage s - 1, before the barrier behind that) and first read during the second.  One tile
+        // per stage: tile i + 2 is parked during tile i.
+        constexpr int kShares = KS * NRBW, kEvery = kShares / kPerThread;
+        auto spread = [&](int set, int stage) __attribute__((always_inline)) {
+            return [&, set, stage](int k) __attribute__((always_inline)) {
+                if (k % kEvery == 0 && k / kEvery < kPerThread) next_stage(set, stage, k / kEvery);
+            };
+        };
+        const auto nothing = [](int) {};
+        fetch_stage(0, 0);
+        fetch_stage(1, 1);
+        all_next(0, 0);
+        if constexpr (TS == 1) all_next(1, 1);
+        // the query rows are there: asked for here, on every path, or the compiler waits for them (and with them for
+        // all loads in flight) in the loop
+#pragma unroll
+        for (int u = 0; u < NRBW; ++u)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qreg[u][ks]));
         __syncthreads();
-        v16f_t acc[2][NRBW];
-        uint32_t bad = 0;
         if (active) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) read_k(ks, 0, 0);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int u = 0; u < NRBW; ++u) mfma(0, u, ks);
             // row references: the maxima of the first tile
-            logits(acc[0], 0, 0);
 #pragma unroll
             for (int u = 0; u < NRBW; ++u) {
                 float mloc = acc[0][u][0];
@@ -524,55 +621,62 @@ __global__ __launch_bounds__(256, 2) void score_tiles_shared_kernel(const _Float
                 for (int v = 1; v < 16; ++v) mloc = fmaxf(mloc, acc[0][u][v]);
                 m_run[u] = xhalf_max(mloc) * g.scale_log2e;
             }
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) read_k(ks, TS == 2 ? 0 : 1, TS == 2 ? 1 : 0);
         }
-        // the MFMAs of tile `tile` (set cur) interleaved with the partials of tile - 1 (set cur ^ 1)
-        auto fast_tile = [&](int cur, int buf, int j, int tile) __attribute__((always_inline)) {
-            if (tile == tile_begin) {
-                logits(acc[cur], buf, j);
-                return;
+        if constexpr (TS == 1) __syncthreads();
+        all_next(TS == 2 ? 1 : 0, TS == 2 ? 1 : 2);
+        __syncthreads();
+        // acc[0] holds tile 2 i of the pass, kreg tile 2 i + 1; TS == 2: that is stage i, in kstage[buf]
+        auto two_tiles = [&](int i, int buf) __attribute__((always_inline)) {
+            const int t = tile_begin + 2 * i + 1;
+            if constexpr (TS == 2) {
+                fast_tile(1, buf ^ 1, 0, t, nothing);
+                fast_tile(0, buf ^ 1, 1, t + 1, spread(buf, i + 2));
+            } else {
+                fast_tile(1, 0, 0, t, spread(1, 2 * i + 3));
+                __syncthreads();
+                fast_tile(0, 1, 0, t + 1, spread(0, 2 * i + 4));
             }
-            logits(acc[cur], buf, j);
-#pragma unroll
-            for (int u = 0; u < NRBW; ++u)
-                fast_epilogue<SBT>(acc[cur ^ 1][u], g.scale_log2e, w_const, m_run[u], l_run[u], bad,
-                                   es_base[u] + static_cast<int64_t>(tile - 1) * SBT * g.rows_p, g.rows_p);
-            // one MFMA, then a share of the VALU work, and so on
-#pragma unroll
-            for (int i = 0; i < KS * NRBW; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x402, (66 + 2 * SBT) / KS + 1, 0);
-            }
-        };
-        // stage s (TS tiles from t) is in kstage[s & 1]; `next` holds stage s + 1, `far` receives
-        // stage s + 2.  Tiles use the accumulator sets in turn: set = (tile - tile_begin) & 1.
-        auto fast_stage = [&](int t, int buf, su4_t (&next)[kPerThread], su4_t (&far)[kPerThread])
-                              __attribute__((always_inline)) {
-            if (t + 2 * TS < fast_end) fetch(far, t + 2 * TS, fast_end);
-            if (active) {
-                if constexpr (TS == 2) {
-                    fast_tile(0, buf, 0, t);
-                    if (t + 1 < fast_end) fast_tile(1, buf, 1, t + 1);
-                } else {
-                    fast_tile(buf, buf, 0, t);
-                }
-            }
-            if (t + TS < fast_end) park(next, buf ^ 1);
             __syncthreads();
         };
-        for (int t = tile_begin; t < fast_end; t += 2 * TS) {
-            fast_stage(t, 0, sa, sb);
-            if (t + TS < fast_end) fast_stage(t + TS, 1, sb, sa);
-        }
+        int i = 0;
         if (active) {
-            // partials of the last tile of the pass
-            const int last = fast_end - 1;
-            const int set = (last - tile_begin) & 1;
-#pragma unroll
-            for (int u = 0; u < NRBW; ++u) {
-                float* es = es_base[u] + static_cast<int64_t>(last) * SBT * g.rows_p;
-                if (set == 0) fast_epilogue<SBT>(acc[0][u], g.scale_log2e, w_const, m_run[u], l_run[u], bad, es, g.rows_p);
-                else fast_epilogue<SBT>(acc[1][u], g.scale_log2e, w_const, m_run[u], l_run[u], bad, es, g.rows_p);
+            for (; 2 * i + 4 < n_fast; i += 2) {
+                two_tiles(i, 0);
+                two_tiles(i + 1, 1);
             }
+            if (2 * i + 2 < n_fast) {           // i is even
+                two_tiles(i, 0);
+                ++i;
+            }
+            const int t = tile_begin + 2 * i;
+            if (2 * i + 1 < n_fast) {           // (what the last call reads ahead is not used)
+                fast_tile(1, 0, 0, t + 1, nothing);
+                last_tile(1, t + 1);
+            } else {
+                last_tile(0, t);
+            }
+        } else {                                // a wavefront without rows only helps with the stages
+            for (; 2 * i + 2 < n_fast; ++i) {
+                if constexpr (TS == 2) {
+                    if (i & 1) all_next(1, i + 2);
+                    else all_next(0, i + 2);
+                } else {
+                    all_next(1, 2 * i + 3);
+                    __syncthreads();
+                    all_next(0, 2 * i + 4);
+                }
+                __syncthreads();
+            }
+            // (the compiler lets this path run into the one above, and would wait there for what it left in flight)
+            __builtin_amdgcn_s_waitcnt(0);
+        }
+        // a sum that left the safe range has taken the run's denominator with it
+        uint32_t bad = 0;
+        if (active) {
+#pragma unroll
+            for (int u = 0; u < NRBW; ++u) bad |= l_run[u] < kRefOverflow ? 0u : 1u;
         }
         dirty = __syncthreads_or(static_cast<int>(bad));
     }
