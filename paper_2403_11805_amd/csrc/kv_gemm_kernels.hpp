@@ -77,11 +77,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t gemm_rows(const _Float16* B, i
 }
 
 // Results of row m, columns n .. n + 7: into the partial product of this split, or the result.
-__device__ __forceinline__ void gemm_store8(const GemmArgs& g, int mat, int m, int n, gv4f_t lo, gv4f_t hi) {
+__device__ __forceinline__ void gemm_store8(const GemmArgs& g, int mat, int split, int m, int n, gv4f_t lo, gv4f_t hi) {
     const int N = g.N[mat];
     const size_t at = static_cast<size_t>(m) * N + n;
     if (g.splits > 1 || g.out_f32) {
-        float* dst = g.splits > 1 ? g.part + g.part_at[mat] + blockIdx.y * (static_cast<size_t>(g.M) * N) : static_cast<float*>(g.C[mat]);
+        float* dst = g.splits > 1 ? g.part + g.part_at[mat] + split * (static_cast<size_t>(g.M) * N) : static_cast<float*>(g.C[mat]);
         *reinterpret_cast<gv4f_t*>(dst + at) = lo;
         *reinterpret_cast<gv4f_t*>(dst + at + 4) = hi;
         return;
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs g) {
                 hi += sums[(k * 32 + r) * (kCols / 4) + 2 * c8 + 1];
             }
             const int m = m0 + b * 32 + r, nn = n0 + 8 * c8;
-            if (m < g.M && nn < N) gemm_store8(g, mat, m, nn, lo, hi);
+            if (m < g.M && nn < N) gemm_store8(g, mat, blockIdx.y, m, nn, lo, hi);
         }
     }
 }
@@ -236,11 +236,13 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs g) {
 // MFMA, so the operand reads, permutes and loads of the next step are dealt out behind the MFMAs of this one, two
 // and two (the scheduling barriers fix that order; left alone the compiler clusters them: 179 against 229 us for
 // the four launches at 304 rows, 1509 against 1851 us at 4096).
-// Measured, the four launches of a Llama-2-7B layer: 304 rows 175 us (the LDS-tiled kernel before it 312), 512 rows
-// 250 (348), 2048 rows 800 us = 1.04 PFLOP/s (the GEMM library's standard choice 1042), 4096 rows 1509 us = 1.10.
+// Measured, the four launches of a Llama-2-7B layer in a kernel trace: 304 rows 210 us (the LDS-tiled kernel before
+// it 312), 512 rows 301 (348), 2048 rows 832 us = 1.00 PFLOP/s (the GEMM library's standard choice 1042).
+// Loading eight columns of two rows per lane and exchanging them between lanes changes nothing (269 and 267 us a
+// layer at 304 rows, 990 and 998 at 2048): the width of the weight loads is not what a step waits for.
 // At few rows a step is bound by its chain of waits (no MFMAs at all: 81 of 92 us for gate | up at 304 rows), at
 // many by the chip's power and by the last round of workgroups.
-// Grid (8 * ceil(column tiles / 8) * row tiles, splits), 256 threads; kGemmStage divides g.steps.
+// Grid 8 * ceil(column tiles * splits / 8) * row tiles, 256 threads; kGemmStage divides g.steps.
 // GATED: two matrices of one width, splits == 1, and the result is C[0] = fp16(silu(A B[0]) * (A B[1])) in fragment
 // order, both products rounded to fp16 first; a column tile is 128 columns of each.
 template <int MB, bool GATED>
@@ -252,19 +254,23 @@ __global__ __launch_bounds__(256, MB <= 4 ? 2 : 1) void gemm_tile_kernel(GemmArg
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, j = lane & 31;
-    // workgroups are dealt to the eight XCDs in turn: the row tiles of one column tile follow each other on one
-    // XCD, whose L2 then serves the column tile's weights to all of them
+    // workgroups are dealt to the eight XCDs in turn: the row tiles of one column tile and split follow each other
+    // on one XCD, whose L2 then serves these weights to all of them.  Splits and column tiles are dealt together:
+    // each split by itself left XCDs short where the column tiles are no multiple of eight (20 of them, six splits,
+    // 512 rows: 36 workgroups for the 32 CUs of four XCDs, 24 for those of the others)
     const int row_tiles = (g.M + MB * 32 - 1) / (MB * 32);
     const int grp = blockIdx.x / (8 * row_tiles), local = blockIdx.x - grp * 8 * row_tiles;
-    const int tile = grp * 8 + (local & 7), m0 = (local >> 3) * MB * 32;
-    if (tile >= g.tile_end[kGemmMaxMats - 1]) return;
+    const int unit = grp * 8 + (local & 7), m0 = (local >> 3) * MB * 32;
+    const int tiles = g.tile_end[kGemmMaxMats - 1];
+    if (unit >= tiles * g.splits) return;
+    const int split = unit / tiles, tile = unit - split * tiles;
     // GATED: wavefronts 0 and 1 hold 128 columns of matrix 0, 2 and 3 the same columns of matrix 1
     const int mat = GATED ? wave >> 1 : (tile >= g.tile_end[0]) + (tile >= g.tile_end[1]);
     const int n0 = GATED ? tile * (kTileCols / 2) + (wave & 1) * 64
                            : (tile - (mat ? g.tile_end[mat - 1] : 0)) * kTileCols + wave * 64;
     const int N = g.N[mat], K = g.K, K8 = K / 8;
     const int s_all = (K + kGemmStep - 1) / kGemmStep;
-    const int sb = blockIdx.y * g.steps, se = min(s_all, sb + g.steps);
+    const int sb = split * g.steps, se = min(s_all, sb + g.steps);
     const int ns = se - sb, n_stages = (ns + kGemmStage - 1) / kGemmStage;
     const bool half_step = (K & 8) && se == s_all;
     const int full = (ns - (half_step ? 1 : 0)) / kGemmStage;      // stages of whole steps only
@@ -469,7 +475,7 @@ __global__ __launch_bounds__(256, MB <= 4 ? 2 : 1) void gemm_tile_kernel(GemmArg
                 const int r = 8 * i + (lane >> 3), c8 = lane & 7;
                 const gv4f_t* src = reinterpret_cast<const gv4f_t*>(tile_lds + r * kPitch + 8 * c8);
                 const int m = m0 + b * 32 + r, n = n0 + 8 * c8;
-                if (m < g.M && n < N) gemm_store8(g, mat, m, n, src[0], src[1]);
+                if (m < g.M && n < N) gemm_store8(g, mat, split, m, n, src[0], src[1]);
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();

@@ -77,9 +77,13 @@ struct OwnGemm {
 // (two per CU and some: gate | up of a Llama-2-7B layer, 16 rows, 34 us with 4 splits, 36 with one) or 256 of two
 // (o, 64 rows, 14.0 us with 8 splits, 14.9 with 6; q | k | v 26 with 2).
 // Above, the row blocks per workgroup (3..8) and the splits that minimise
-//     rounds of 256 workgroups * steps * (0.13 + 0.045 * row blocks) us + 6 us, not less than the weights at
-//     4.8 TB/s, + writing and reading the partial products at 5 TB/s each,
-// with the cost of a step fitted to launches of 128 .. 4096 rows (row blocks 4, 5, 8: 0.31, 0.35, 0.49 us).
+//     rounds of 256 workgroups * steps * (0.184 + 0.0453 * row blocks) us
+//     + writing and reading the partial products at 3.25 TB/s each;
+// up to four row blocks a CU holds two workgroups, and two full rounds together cost 1.72 of one.  Fitted to all
+// row blocks and splits of the four launches of layers of width 1024, 4096 and 5120 at 80 .. 2048 rows (28 layers):
+// the choice costs a launch 0.3 % of its layer's time on average over the fastest one (a rule without the discount,
+// with 5 TB/s and a floor for the weights' bytes: 0.5 %; down, 4096 wide, d_ff 14336, 512 rows, a layer in all: 4
+// splits of 4 row blocks 340 us, that rule's 8 splits of 8 row blocks 348).
 // `room` bytes are there for partial products.
 OwnGemm own_gemm_plan(int64_t M, const int64_t* N, int n_mats, int64_t K, uint64_t room) {
     OwnGemm best{};
@@ -106,14 +110,15 @@ OwnGemm own_gemm_plan(int64_t M, const int64_t* N, int n_mats, int64_t K, uint64
     }
     double least = 0.0;
     for (int mb = 3; mb <= 8; ++mb) {
-        const int64_t row_tiles = (M + 32 * mb - 1) / (32 * mb), groups = tiles(kTileCols) * row_tiles;
+        const int64_t row_tiles = (M + 32 * mb - 1) / (32 * mb);
         for (int64_t s = 1; s <= kGemmMaxSplits && (s == 1 || (s <= room_splits && steps / s >= 2 * kGemmStage)); ++s) {
             const int64_t each = ((steps + s - 1) / s + kGemmStage - 1) / kGemmStage * kGemmStage;
             const int64_t splits = (steps + each - 1) / each;
-            const double rounds = static_cast<double>((groups * splits + 255) / 256);
-            double us = rounds * static_cast<double>(each) * (0.13 + 0.045 * mb) + 6.0;
-            us = std::max(us, static_cast<double>(K * n_sum) * 2.0 / 4.8e6);
-            if (splits > 1) us += 2.0 * static_cast<double>(splits * part) / 5e6;
+            const int64_t groups = (tiles(kTileCols) * splits + 7) / 8 * 8 * row_tiles;
+            double rounds = static_cast<double>((groups + 255) / 256);
+            if (mb <= 4) rounds -= 0.28 * static_cast<double>(groups / 512);
+            double us = rounds * static_cast<double>(each) * (0.184 + 0.0453 * mb);
+            if (splits > 1) us += 2.0 * static_cast<double>(splits * part) / 3.25e6;
             if (best.mb == 0 || us < least) {
                 least = us;
                 best.mb = mb;
@@ -322,9 +327,9 @@ int own_gemm(hipStream_t st, int64_t M, int64_t K, const void* A, const GemmGrou
         if (h.mb == 1) hipLaunchKernelGGL(gemm_stream_kernel<1>, grid, dim3(256), 0, st, g);
         else hipLaunchKernelGGL(gemm_stream_kernel<2>, grid, dim3(256), 0, st, g);
     } else {
-        const int64_t blocks = static_cast<int64_t>((h.col_tiles + 7) / 8 * 8) * h.row_tiles;
+        const int64_t blocks = (static_cast<int64_t>(h.col_tiles) * h.splits + 7) / 8 * 8 * h.row_tiles;
         if (blocks > 0x7fffffffLL) return fail(KV_ESHAPE, "GEMM (%s): grid exceeds 2^31 workgroups", what);
-        const dim3 grid(static_cast<uint32_t>(blocks), static_cast<uint32_t>(h.splits));
+        const dim3 grid(static_cast<uint32_t>(blocks));
 #define KV_TILE(MB)                                                                                       \
     do {                                                                                                  \
         if (gated) hipLaunchKernelGGL((gemm_tile_kernel<MB, true>), grid, dim3(256), 0, st, g);           \

@@ -24,6 +24,7 @@ def some(n, of, seed):
     (1, 2, 4, 64, 1024, 16, 136, 1032, 0, some(46, 64, 4)),      # 736 rows; too short a K to divide: gate and up gated in one
     (1, 1, 2, 64, 512, 8, 56, 136, 0, some(29, 64, 5)),          # 232 rows, gated: an odd number of row blocks, the last of 8
     (1, 1, 1, 64, 256, 8, 64, 8, 0, some(12, 32, 6)),            # 96 rows, gated: one piece of columns
+    (1, 1, 2, 64, 256, 8, 2568, 1288, 0, some(20, 32, 7)),       # 160 rows, K divided over 11 column tiles: XCDs shared by splits
 ])
 def test_projection_edges(case):
     run_case(*case, seed=71)
