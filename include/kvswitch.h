@@ -489,7 +489,7 @@ typedef struct {
 /* Handle of the recompute path.  The projections of up to KV_RECOMPUTE_OWN_GEMM_ROWS recomputed
  * tokens (what a plan of Eq. 4 recomputes beside a Load) run on the library's own MFMA GEMM,
  * which is the faster one there (per Llama-2-7B layer 0.18 ms at 128 tokens, 0.27 at 304, 0.34 at 512;
- * at 2048 0.98 against 1.21 ms with rocBLAS); larger ones are handed
+ * at 2048 0.96 against 1.21 ms with rocBLAS); larger ones are handed
  * to rocBLAS, which is loaded on creation if it is installed (the handle then owns that
  * library's handle, whose device workspace lives until kv_recompute_destroy).  Without
  * rocBLAS, or with KVSWITCH_OWN_GEMM=1 in the environment at creation, every size runs on the
