@@ -871,7 +871,8 @@ __global__ __launch_bounds__(256, 4) void score_head_kernel(const _Float16* __re
 // partials, then the chunk masses from the per-tile partials.  `parts` workgroups
 // divide the chunks of a head among themselves so that long contexts keep enough
 // wavefronts in flight.
-constexpr int kCombineMaxRuns = 8192;       // runs per head the combine kernel keeps a bit for (host-checked)
+constexpr int kCombineMaxRuns = 8192;       // runs per head the combine kernel keeps bits for (host-checked)
+constexpr int kCombineMaxBlocks = 8;        // blocks of 32 query rows per head (rows_p <= 256)
 
 __global__ __launch_bounds__(256, 8) void score_combine_kernel(ScoreGeom g, ScoreWs ws,
                                                             float* __restrict__ chunk_mass) {
@@ -933,25 +934,28 @@ __global__ __launch_bounds__(256, 8) void score_combine_kernel(ScoreGeom g, Scor
     const int n_sb = g.N / g.sb_tokens;
     const float* es = ws.e_sub + static_cast<int64_t>(lh) * n_sb * g.rows_p;
     const int grp = tid >> 4, gl = tid & 15;
-    // tiles of a run below the causal diagonal share the run's fast reference where there is one:
-    // one bit per run (the decision is the same for every row of a head), so that the choice
-    // between the two planes is known before either is loaded
+    // tiles of a run below the causal diagonal share the run's fast reference where there is one: one bit per run and
+    // block of 32 rows, so that the choice between the two planes is known before either is loaded.  The workgroup of
+    // the tile kernel decides for all its rows, but the blocks of a head may lie in two workgroups (at head_dim 256
+    // one holds four blocks, otherwise eight)
     const float* mf = ws.m_fast + static_cast<int64_t>(lh) * g.n_runs * g.rows_p;
     const int first_tail_tile = (g.Nv - g.R + 1) / 32;
     // run_len is a power of two whenever a head has more than one run; sb_per_tile is 1, 2 or 4
     const int run_shift = g.n_runs > 1 ? __builtin_ctz(static_cast<unsigned>(g.run_len)) : 31;
     const int sbt_shift = __builtin_ctz(static_cast<unsigned>(sb_per_tile));
-    __shared__ uint32_t fast_bits[kCombineMaxRuns / 32];
+    __shared__ uint32_t fast_bits[kCombineMaxBlocks * kCombineMaxRuns / 32];
+    const int bits_pitch = (g.n_runs + 63) / 64 * 2;         // words per row block
     // one run per lane, the wavefront's 64 answers collected by a ballot (loads side by side, not in turn)
-    for (int t0 = tid & ~63; t0 < g.n_runs; t0 += 256) {
-        const int t = t0 + (tid & 63);
-        const float v = mf[static_cast<int64_t>(min(t, g.n_runs - 1)) * g.rows_p];   // row 0 exists in every head
-        const uint64_t ok = __ballot(t < g.n_runs && v == v);
-        if ((tid & 63) == 0) {
-            fast_bits[t0 >> 5] = static_cast<uint32_t>(ok);
-            fast_bits[(t0 >> 5) + 1] = static_cast<uint32_t>(ok >> 32);
+    for (int rb = 0; rb < g.RB; ++rb)
+        for (int t0 = tid & ~63; t0 < g.n_runs; t0 += 256) {
+            const int t = t0 + (tid & 63);
+            const float v = mf[static_cast<int64_t>(min(t, g.n_runs - 1)) * g.rows_p + rb * 32];   // its first row exists
+            const uint64_t ok = __ballot(t < g.n_runs && v == v);
+            if ((tid & 63) == 0) {
+                fast_bits[rb * bits_pitch + (t0 >> 5)] = static_cast<uint32_t>(ok);
+                fast_bits[rb * bits_pitch + (t0 >> 5) + 1] = static_cast<uint32_t>(ok >> 32);
+            }
         }
-    }
     __syncthreads();
     // two chunks per group and pass, all their loads issued before the arithmetic: 62 registers, eight
     // wavefronts per SIMD (four chunks at four wavefronts per SIMD measured 10 % slower)
@@ -972,8 +976,8 @@ __global__ __launch_bounds__(256, 8) void score_combine_kernel(ScoreGeom g, Scor
                     const int sb = c * sb_per_chunk + k;
                     const int tile = sb >> sbt_shift;
                     const int rn = tile >> run_shift;
-                    // (uniform per group: a chunk's sub-block lies in one tile)
-                    const bool fast = tile < first_tail_tile && ((fast_bits[rn >> 5] >> (rn & 31)) & 1u);
+                    // (a chunk's sub-block lies in one tile, the lane's four rows in one block)
+                    const bool fast = tile < first_tail_tile && ((fast_bits[(rr >> 5) * bits_pitch + (rn >> 5)] >> (rn & 31)) & 1u);
                     mi[u] = *reinterpret_cast<const float4*>(fast ? mf + static_cast<int64_t>(rn) * g.rows_p + rr
                                                                   : mt + static_cast<int64_t>(tile) * g.rows_p + rr);
                     e[u] = *reinterpret_cast<const float4*>(es + static_cast<int64_t>(sb) * g.rows_p + rr);

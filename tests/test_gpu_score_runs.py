@@ -80,3 +80,33 @@ def test_workspace_that_holds_the_longest_runs_only(geom, R, longest):
     with pytest.raises(kvs.KvError) as err:
         score_with(ks, q, kv, g.N, least - 1)
     assert err.value.code == kvs.KV_ENOMEM
+
+
+@pytest.mark.parametrize("per,D,R,hot_block", [
+    (1, 256, 256, 2), (1, 256, 256, 6),      # one head of eight blocks in two workgroups of four
+    (2, 256, 96, 3), (2, 256, 96, 5),        # the second head: its first block in one workgroup, two in the next
+    (4, 128, 96, 7), (4, 128, 96, 8),        # the third head: two blocks in one workgroup of eight, one in the next
+    (4, 64, 96, 6), (4, 64, 96, 8),
+])
+@pytest.mark.parametrize("norm", [oracle.NORM_VISIBLE, oracle.NORM_NONE])
+def test_reference_left_by_one_row_block(per, D, R, hot_block, norm):
+    """A head whose row blocks lie in two workgroups, and a key that the queries of only one block answer to, far
+    above the reference of its run: one workgroup redoes the run, the other does not, and every row has to be
+    combined with the references of its own workgroup."""
+    hot_token = 200
+    g = synth.Geometry(1, 1, per, D, 1024, 16, 64)
+    ks, os_ = both_shapes(g)
+    kv = (synth.make_kv(g, 37, "cpu").float() * 0.05).to(torch.float16)
+    kv[0, 0, 0, hot_token] = 20.0
+    q = torch.full((1, per, R, D), 2.0, dtype=torch.float16)
+    q[..., ::2] = -2.0                       # nothing to the hot key: its channels are all alike
+    blocks = (R + 31) // 32
+    rows = slice(hot_block % blocks * 32, min(hot_block % blocks * 32 + 32, R))
+    q[0, hot_block // blocks, rows] = 2.0
+    want = oracle.score_chunks(os_, q.numpy(), kv.numpy(), norm)
+    ws = torch.full((kvs.kv_score_workspace_bytes(ks, R),), 0xff, dtype=torch.uint8, device=DEV)
+    cm = torch.full((1, per, ks.n_chunks), float("nan"), dtype=torch.float32, device=DEV)
+    d = torch.full((ks.n_chunks,), float("nan"), dtype=torch.float32, device=DEV)
+    kvs.kv_score_chunks(ks, q.to(DEV), kv.to(DEV), norm, ws, cm, d)
+    torch.cuda.synchronize()
+    check((cm.cpu().numpy(), d.cpu().numpy()), want)
