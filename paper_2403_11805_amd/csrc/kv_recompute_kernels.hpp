@@ -368,7 +368,9 @@ __global__ __launch_bounds__(64 * kAttnWaves, 2) void recompute_attention_kernel
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
             const int p = min(i * kThreads + tid, kTilePieces - 1);       // surplus threads repeat the last piece
-            const int token = min(t * 32 + p / kRowPieces, g.N - 1);      // rows past the cache are masked anyway
+            // tokens behind the workgroup's last row are masked, but their V is still multiplied, by a probability of
+            // 0, and the cache may hold anything there (NaN too): the last row's token takes their place
+            const int token = min(t * 32 + p / kRowPieces, wg_max_pos);
             const int64_t src = static_cast<int64_t>(token) * kRowPieces + p % kRowPieces;
             kst[set][i] = kbase[src];
             vst[set][i] = vbase[src];

@@ -45,3 +45,35 @@ def test_reference_moves_and_ranges_differ(Hkv, Hq, D, N, missing, hot):
     rc.close()
     err = close(y.cpu().numpy(), y_ref, 1e-2, 1e-2, "layer output")
     assert err < 3e-3
+
+
+@pytest.mark.parametrize("Hkv,Hq,D,N,T,missing", [
+    (1, 4, 128, 128, 8, [2, 5]),             # undivided; the last row is token 47 of tile 32..63
+    (1, 2, 64, 96, 16, [0, 2]),              # undivided; token 47 again, the cache ends a tile later
+    (1, 4, 128, 1024, 16, [3, 20, 40]),      # divided: token 655 of tile 640..671
+    (8, 8, 64, 1024, 8, [1, 64, 100]),       # divided, kv heads dealt to the XCDs: token 807 of tile 800..831
+])
+def test_nothing_behind_the_last_token_is_used(Hkv, Hq, D, N, T, missing):
+    """The cache has to hold what lies before the last recomputed token; what lies behind it, in the last tile of keys
+    too, may be anything (NaN here)."""
+    d_model, d_ff = 256, 512
+    shape = kvs.Shape(1, Hkv, Hq, D, N, T, 64)
+    dims_o = orc.LayerDims(d_model, Hq, Hkv, D, d_ff)
+    dims = binding.LayerDims(d_model, d_ff, dims_o.rope_base, dims_o.rms_eps)
+    w = synth.make_layer_weights(d_model, Hq, Hkv, D, d_ff, 89)
+    kv = synth.make_kv(synth.Geometry(1, Hkv, Hq, D, N, T, 64), 89, "cpu")
+    rows = np.concatenate([np.arange(c * T, (c + 1) * T) for c in missing])
+    x = synth.make_hidden(len(rows), d_model, 89)
+    k_ref, v_ref = kv[0, 0].numpy().copy(), kv[0, 1].numpy().copy()
+    y_ref = orc.recompute_layer(x.numpy(), missing, T, k_ref, v_ref, {k: v.numpy() for k, v in w.items()}, dims_o)
+    kv_dev = kv.to(DEV)
+    kv_dev[:, :, :, rows[-1] + 1:] = float("nan")
+    y = torch.full((len(rows), d_model), float("nan"), dtype=torch.float16, device=DEV)
+    ws = torch.empty(kvs.kv_recompute_workspace_bytes(shape, dims, len(missing)), dtype=torch.uint8, device=DEV)
+    rc = kvs.Recompute()
+    rc.layer(shape, dims, {k: v.to(DEV) for k, v in w.items()}, 0,
+             torch.tensor(missing, dtype=torch.int32, device=DEV), x.to(DEV), kv_dev, y, ws)
+    torch.cuda.synchronize()
+    rc.close()
+    err = close(y.cpu().numpy(), y_ref, 1e-2, 1e-2, "layer output")
+    assert err < 3e-3
