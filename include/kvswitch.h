@@ -257,7 +257,11 @@ uint64_t kv_score_workspace_bytes(const kv_shape_t* shape, int32_t n_queries);
  *   density    dev fp32 [n_chunks]: mean of chunk_mass over layers and heads,
  *        divided by chunk_tokens (= D_i of Eq. 1).
  *   workspace  dev, >= kv_score_workspace_bytes(), 256-byte aligned; contents
- *        are scratch. */
+ *        are scratch, and the results do not depend on its size.  Where few heads over
+ *        a short context are scored in shorter runs of tiles, a workspace of up to
+ *        1.5 MiB less, which holds the partials of the longest runs, is served too
+ *        (anything less: KV_ENOMEM); the sums are then added in another order, so that
+ *        the last bits of a density, and the rank of chunks that all but tie, may differ. */
 int32_t kv_score_chunks(const kv_shape_t* shape, const void* q, int32_t n_queries,
                         const void* kv, int32_t norm_mode,
                         void* workspace, uint64_t workspace_bytes,
@@ -280,16 +284,16 @@ int32_t kv_score_chunks_valid(const kv_shape_t* shape, const void* q, int32_t n_
 
 /* kv_score_chunks for callers that cannot allocate device memory and so have no workspace to
  * hand over: code running under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc.  The partial results live in a static device array of KV_SCORE_STATIC_BYTES that
- * every GPU the library runs on holds until the process ends; the call allocates and frees
+ * hipMalloc.  The partial results live in a static device array of KV_SCORE_STATIC_BYTES (and 2 MiB)
+ * that every GPU the library runs on holds until the process ends; the call allocates and frees
  * nothing (its first call on a device looks the array's address up).  Same arguments and
- * results as kv_score_chunks without the workspace pair.  A shape whose scoring needs more
- * scratch than the array holds is refused with KV_ENOMEM (kv_score_workspace_bytes tells; a
- * shape that one workgroup per head scores in LDS - one block of query rows per head and at
- * least 256 (layer, head) pairs, e.g. a 4096-token multi-head cache - needs none).  All calls
- * on one GPU share that GPU's array: calls that overlap in time on one GPU (two streams, two
- * threads) race and give undefined results; calls one after the other on a stream need no
- * clearing in between. */
+ * results, to the bit, as kv_score_chunks without the workspace pair.  A shape whose partials over
+ * the longest runs of tiles exceed KV_SCORE_STATIC_BYTES is refused with KV_ENOMEM (none is refused
+ * whose kv_score_workspace_bytes is at most that; a shape that one workgroup per head scores in
+ * LDS - one block of query rows per head and at least 256 (layer, head) pairs, e.g. a 4096-token
+ * multi-head cache - needs none).  All calls on one GPU share that GPU's array: calls that overlap
+ * in time on one GPU (two streams, two threads) race and give undefined results; calls one after
+ * the other on a stream need no clearing in between. */
 #define KV_SCORE_STATIC_BYTES (32u << 20)
 int32_t kv_score_chunks_static(const kv_shape_t* shape, const void* q, int32_t n_queries,
                                const void* kv, int32_t norm_mode,

@@ -483,8 +483,11 @@ static uint64_t score_head_lds_bytes(const ScoreGeom& g, int head_dim) {
 }
 
 // The geometry to launch with, given `available` bytes of scratch.  Shorter runs need a little more (three floats
-// per row and run); a workspace that holds the longest runs only - one made for another shape, or the static
-// array - is served with these, as long as it holds them.
+// per row and run); a workspace that holds the longest runs only - one made for another shape - is served with
+// these, as long as it holds them.  How much more: the last halving starts from at most 255 workgroups of a run and up
+// to eight row blocks each (K shared), or from 127 of four runs and two row blocks, and it doubles the runs: 3 floats *
+// 510 * 256 rows = 1.5 MiB at the most.
+constexpr uint64_t kShortRunsExtraBytes = 2u << 20;
 static ScoreGeom fitted_runs(const ScoreGeom& g, int head_dim, uint64_t available) {
     if (score_head_lds_bytes(g, head_dim)) return g;
     ScoreGeom s = g;
@@ -533,7 +536,9 @@ int32_t kv_score_chunks_valid(const kv_shape_t* shape, const void* q, int32_t n_
 // Scratch of kv_score_chunks_static: one copy per GPU the library runs on, held until the process
 // ends.  In host code the name is only a handle; the device address comes from
 // hipGetSymbolAddress, once per device.
-constexpr uint64_t kStaticScratchBytes = KV_SCORE_STATIC_BYTES;
+// What is accepted goes by the longest runs; beside these the array has room for the planes of shorter ones, so that
+// the runs, and with them the order of the sums, are those of a call with a workspace.
+constexpr uint64_t kStaticScratchBytes = KV_SCORE_STATIC_BYTES + kShortRunsExtraBytes;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -565,10 +570,10 @@ int32_t kv_score_chunks_static(const kv_shape_t* shape, const void* q, int32_t n
     if (!aligned(q, 16) || !aligned(kv, 16)) return fail(KV_EINVAL, "q/kv must be 16-byte aligned");
     // a head scored by one workgroup keeps its partials in LDS and needs no scratch at all
     const uint64_t need = score_head_lds_bytes(g, shape->head_dim) ? 0 : score_ws_bytes(g);
-    if (need > kStaticScratchBytes)
+    if (need > KV_SCORE_STATIC_BYTES)
         return fail(KV_ENOMEM, "scoring this shape needs %llu bytes of scratch, the static buffer holds %llu: "
                     "use kv_score_chunks with a workspace",
-                    static_cast<unsigned long long>(need), static_cast<unsigned long long>(kStaticScratchBytes));
+                    static_cast<unsigned long long>(need), static_cast<unsigned long long>(KV_SCORE_STATIC_BYTES));
     void* ws = nullptr;
     if (int rc = static_scratch(&ws)) return rc;
     // every slot of the partial planes is written before it is read: nothing has to start at zero

@@ -110,3 +110,20 @@ def test_reference_left_by_one_row_block(per, D, R, hot_block, norm):
     kvs.kv_score_chunks(ks, q.to(DEV), kv.to(DEV), norm, ws, cm, d)
     torch.cuda.synchronize()
     check((cm.cpu().numpy(), d.cpu().numpy()), want)
+
+
+def test_static_array_gives_the_same_bits():
+    """A shape whose longest runs just fit the static array's promised size, and whose shorter ones need more: the
+    call without a workspace still gives the bits of the call with one."""
+    g = synth.Geometry(1, 1, 8, 64, 128000, 32, 64)
+    ks, _ = both_shapes(g)
+    R = 128
+    assert kvs.kv_score_workspace_bytes(ks, R) > kvs.KV_SCORE_STATIC_BYTES
+    kv = synth.make_kv(g, 41, DEV)
+    q = synth.make_q(g, 41, R, DEV)
+    cm = torch.full((1, 8, ks.n_chunks), float("nan"), dtype=torch.float32, device=DEV)
+    d = torch.full((ks.n_chunks,), float("nan"), dtype=torch.float32, device=DEV)
+    kvs.kv_score_chunks_static(ks, q, kv, oracle.NORM_VISIBLE, cm, d)
+    torch.cuda.synchronize()
+    want_cm, want_d = gpu_score(ks, q, kv, oracle.NORM_VISIBLE)
+    assert np.array_equal(cm.cpu().numpy(), want_cm) and np.array_equal(d.cpu().numpy(), want_d)

@@ -384,6 +384,28 @@ def test_scoring_refuses_contexts_beyond_its_run_table():
     assert kvs.kv_score_workspace_bytes(grouped, 32) > 0
 
 
+def test_shorter_scoring_runs_need_little_more_scratch():
+    """kv_score_workspace_bytes exceeds what the longest runs of tiles need by 1.5 MiB at the most (the static array of
+    kv_score_chunks_static holds 2 MiB beside the longest runs), never falls below it, and is the same where one
+    workgroup per head scores in LDS."""
+    rng = np.random.default_rng(97)
+    largest = 0
+    for _ in range(4000):
+        Hkv, per = int(rng.integers(1, 33)), int(rng.choice([1, 1, 2, 3, 4, 5, 8, 16]))
+        L, D, T = int(rng.choice([1, 1, 2, 4, 18, 32])), int(rng.choice([64, 128, 256])), int(rng.choice([8, 16, 32, 64]))
+        N = 64 * int(2 ** rng.uniform(0, 13))
+        R = int(rng.integers(1, min(N, 256) + 1))
+        rows, tiles = (R + 31) // 32 * 32, N // 32
+        n_rb = per * rows // 32
+        longest = 8 if n_rb == 1 or n_rb == 2 else 64
+        runs = -(-tiles // longest)
+        least = (4 * L * Hkv * per * rows * (tiles + N // min(T, 32) + 3 * runs) + 255) // 256 * 256
+        got = kvs.kv_score_workspace_bytes(kvs.Shape(L, Hkv, Hkv * per, D, N, T, 64), R)
+        assert least <= got <= least + (3 << 19), (L, Hkv, per, D, N, T, R)
+        largest = max(largest, got - least)
+    assert largest > 1 << 19, "no shape came near the bound"
+
+
 def test_pipeline_split_matches_oracle():
     rng = np.random.default_rng(31)
     for fmt in (0, 3):
