@@ -176,9 +176,15 @@ def _dev_or_pinned(t: torch.Tensor, dtype=None) -> int:
     return t.data_ptr()
 
 
+# not part of torch's documented interface: where it is absent the documented call takes its place
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
-    if stream is None:                       # without a Stream object per call
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if stream is None:
+        if _raw_stream is None:
+            return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(torch.cuda.current_device())      # without a Stream object per call
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)

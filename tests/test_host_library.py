@@ -2,11 +2,14 @@
 symbol, rejects bad arguments without touching a GPU, and its bookkeeping
 (offsets, bit-widths, gather lists, LCTRU) is identical to the oracle's."""
 import ctypes
+import importlib.util
 import os
 import re
+from types import SimpleNamespace
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import paper_2403_11805_amd as kvs
@@ -382,6 +385,18 @@ def test_scoring_refuses_contexts_beyond_its_run_table():
         kvs.kv_score_workspace_bytes(one._replace(n_tokens=2097152 + 1024), 32)
     grouped = kvs.Shape(1, 1, 4, 64, 4194304, 1024, 64)
     assert kvs.kv_score_workspace_bytes(grouped, 32) > 0
+
+
+def test_current_stream_without_the_private_lookup(monkeypatch):
+    """On a torch without its private raw-stream call the binding takes the documented one."""
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=0x1230))
+    spec = importlib.util.spec_from_file_location("paper_2403_11805_amd.binding_again", binding.__file__)
+    again = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(again)
+    assert again._stream(None) == 0x1230
+    assert again._stream(77) == 77
 
 
 def test_shorter_scoring_runs_need_little_more_scratch():
