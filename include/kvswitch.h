@@ -497,7 +497,9 @@ typedef struct {
  * to rocBLAS, which is loaded on creation if it is installed (the handle then owns that
  * library's handle, whose device workspace lives until kv_recompute_destroy).  Without
  * rocBLAS, or with KVSWITCH_OWN_GEMM=1 in the environment at creation, every size runs on the
- * library's own kernel (1.1 PFLOP/s at 4096 rows).  NULL on
+ * library's own kernel (1.1 PFLOP/s at 4096 rows).  KVSWITCH_GEMM_TILE=<row blocks 3..8>,<splits 1..16>
+ * in the environment at creation takes the choice of that kernel's launch shape above 64 rows from the library, as
+ * far as K and the workspace allow the splits (tests and measurements; another value fails).  NULL on
  * failure (kv_last_error has the text).  One handle serves one stream at a time. */
 #define KV_RECOMPUTE_OWN_GEMM_ROWS 2048
 typedef struct kv_recompute kv_recompute_t;

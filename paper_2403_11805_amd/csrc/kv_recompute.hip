@@ -13,6 +13,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <cstdio>
 #include <cstdlib>
 #include <new>
 #include <vector>
@@ -84,8 +85,12 @@ struct OwnGemm {
 // the choice costs a launch 0.3 % of its layer's time on average over the fastest one (a rule without the discount,
 // with 5 TB/s and a floor for the weights' bytes: 0.5 %; down, 4096 wide, d_ff 14336, 512 rows, a layer in all: 4
 // splits of 4 row blocks 340 us, that rule's 8 splits of 8 row blocks 348).
-// `room` bytes are there for partial products.
-OwnGemm own_gemm_plan(int64_t M, const int64_t* N, int n_mats, int64_t K, uint64_t room) {
+// `room` bytes are there for partial products.  A handle may fix the row blocks and the splits of the tiled launches
+// (`fixed`; as many splits as room and K allow).
+struct FixedTile {
+    int row_blocks = 0, splits = 0;     // 0: chosen
+};
+OwnGemm own_gemm_plan(int64_t M, const int64_t* N, int n_mats, int64_t K, uint64_t room, FixedTile fixed) {
     OwnGemm best{};
     int64_t n_sum = 0;
     for (int j = 0; j < n_mats; ++j) n_sum += N[j];
@@ -109,9 +114,12 @@ OwnGemm own_gemm_plan(int64_t M, const int64_t* N, int n_mats, int64_t K, uint64
         return best;
     }
     double least = 0.0;
+    const int64_t most = std::max<int64_t>(1, std::min<int64_t>(room_splits, steps / (2 * kGemmStage)));
+    const int64_t s_from = fixed.splits ? std::min<int64_t>(fixed.splits, most) : 1, s_to = fixed.splits ? s_from : most;
     for (int mb = 3; mb <= 8; ++mb) {
+        if (fixed.row_blocks && mb != fixed.row_blocks) continue;
         const int64_t row_tiles = (M + 32 * mb - 1) / (32 * mb);
-        for (int64_t s = 1; s <= kGemmMaxSplits && (s == 1 || (s <= room_splits && steps / s >= 2 * kGemmStage)); ++s) {
+        for (int64_t s = s_from; s <= s_to; ++s) {
             const int64_t each = ((steps + s - 1) / s + kGemmStage - 1) / kGemmStage * kGemmStage;
             const int64_t splits = (steps + each - 1) / each;
             const int64_t groups = (tiles(kTileCols) * splits + 7) / 8 * 8 * row_tiles;
@@ -247,6 +255,7 @@ struct kv_recompute {
     rb_gemm_ex_fn gemm_ex = nullptr;
     rb_get_solutions_fn get_solutions = nullptr;     // optional
     std::vector<std::pair<GemmShape, int>> tuned;    // shapes kv_recompute_tune examined: kernel, or -1 = standard
+    FixedTile fixed;                                 // KVSWITCH_GEMM_TILE
 };
 
 namespace {
@@ -286,14 +295,14 @@ enum class Out { kF32, kF16, kGate };
 
 // The library's own GEMM (kv_gemm_kernels.hpp) over a group of weight matrices; A in fragment order.  Without
 // `left` (one matrix only) a divided product is added here.
-int own_gemm(hipStream_t st, int64_t M, int64_t K, const void* A, const GemmGroup& grp, const void* Cin, Out out,
-             Room room, Product* left, const char* what) {
+int own_gemm(hipStream_t st, FixedTile fixed, int64_t M, int64_t K, const void* A, const GemmGroup& grp, const void* Cin,
+             Out out, Room room, Product* left, const char* what) {
     if (!left && grp.n != 1) return fail(KV_EINVAL, "GEMM (%s): a group is added by its reader", what);
     if (K % 8 || K < 8 || M < 1 || grp.n < 1 || grp.n > kGemmMaxMats || (Cin && grp.n != 1))
         return fail(KV_ESHAPE, "GEMM (%s): unsupported shape", what);
     for (int j = 0; j < grp.n; ++j)
         if (grp.N[j] % 8 || grp.N[j] < 8) return fail(KV_ESHAPE, "GEMM (%s) needs N a multiple of 8", what);
-    OwnGemm h = own_gemm_plan(M, grp.N, grp.n, K, room.bytes);
+    OwnGemm h = own_gemm_plan(M, grp.N, grp.n, K, room.bytes, fixed);
     const bool gated = out == Out::kGate && !h.stream && h.splits == 1;
     if (gated) h.col_tiles = static_cast<uint32_t>((grp.N[0] + kTileCols / 2 - 1) / (kTileCols / 2));
     const int64_t cols = h.stream ? kStreamCols : kTileCols;
@@ -360,7 +369,7 @@ bool own_projections(const kv_recompute* rc, int64_t M) { return M <= kOwnGemmRo
 // library per matrix (A and the results row-major).
 int gemm(kv_recompute* rc, hipStream_t stream, int64_t M, int64_t K, const void* A, const GemmGroup& grp, const void* Cin,
          Out out, Room room, Product* left, const char* what) {
-    if (own_projections(rc, M)) return own_gemm(stream, M, K, A, grp, Cin, out, room, left, what);
+    if (own_projections(rc, M)) return own_gemm(stream, rc->fixed, M, K, A, grp, Cin, out, room, left, what);
     if (left) *left = {1, nullptr, false};
     for (int j = 0; j < grp.n; ++j) {
         const GemmShape g = {M, grp.N[j], K, out == Out::kF32, Cin != nullptr};
@@ -483,6 +492,17 @@ kv_recompute_t* kv_recompute_create(void) {
     if (!rc) {
         fail(KV_ENOMEM, "out of host memory");
         return nullptr;
+    }
+    // KVSWITCH_GEMM_TILE=<row blocks>,<splits> fixes the launch shape of the library's own kernel above 64 rows
+    if (const char* tile = getenv("KVSWITCH_GEMM_TILE")) {
+        int blocks = 0, splits = 0, end = 0;
+        if (sscanf(tile, "%d,%d%n", &blocks, &splits, &end) != 2 || tile[end] || blocks < 3 || blocks > 8 || splits < 1 ||
+            splits > kGemmMaxSplits) {
+            fail(KV_EINVAL, "KVSWITCH_GEMM_TILE=%s: want <row blocks 3..8>,<splits 1..%d>", tile, kGemmMaxSplits);
+            delete rc;
+            return nullptr;
+        }
+        rc->fixed = {blocks, splits};
     }
     // KVSWITCH_OWN_GEMM=1 in the environment keeps the GEMM library out: every projection then runs
     // on the library's own kernel, as it does where rocBLAS is not installed

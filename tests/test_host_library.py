@@ -145,6 +145,18 @@ def test_recompute_entry_points_validate_on_the_host():
     binding.lib().kv_recompute_destroy(None)      # a no-op
 
 
+@pytest.mark.parametrize("value,ok", [("3,1", True), ("8,16", True), ("2,1", False), ("9,1", False), ("4,0", False),
+                                      ("4,17", False), ("4", False), ("4,2x", False), ("", False)])
+def test_recompute_tile_from_the_environment(value, ok, monkeypatch):
+    monkeypatch.setenv("KVSWITCH_OWN_GEMM", "1")
+    monkeypatch.setenv("KVSWITCH_GEMM_TILE", value)
+    if ok:
+        kvs.Recompute().close()
+    else:
+        with pytest.raises(kvs.KvError, match="KVSWITCH_GEMM_TILE"):
+            kvs.Recompute()
+
+
 def test_bits_from_scores_matches_oracle_including_ties():
     rng = np.random.default_rng(0)
     for n in (1, 2, 3, 7, 256, 1024):
