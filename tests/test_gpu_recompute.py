@@ -108,16 +108,28 @@ def test_llama_like_layer_sampled_positions():
 
 
 def test_tuned_gemm_kernels_keep_parity():
-    """kv_recompute_tune picks other GEMM kernels for the projections; the layer stays within
-    the same bars of the oracle (a small case and the wider one)."""
+    """kv_recompute_tune where no projection goes to the GEMM library (64 and 816 rows): it leaves the layer as it is.
+    (Where it picks kernels: test_rows_beyond_the_own_gemm_limit.)"""
     run_case(2, 2, 4, 64, 256, 16, 256, 512, 1, [2, 4, 5, 11], seed=41, tune=True)
     run_case(1, 8, 8, 128, 2048, 16, 1024, 2816, 0,
              sorted(np.random.default_rng(7).choice(128, size=51, replace=False).tolist()), seed=43, tune=True)
 
 
+@pytest.mark.parametrize("tune", [False, True])
+@pytest.mark.parametrize("case", [
+    # 2080 of 2304 rows: row-major activations all the way
+    (1, 1, 1, 64, 2304, 16, 72, 136, 0, sorted(np.random.default_rng(11).choice(144, size=130, replace=False).tolist())),  # divided attention
+    (1, 4, 16, 64, 2304, 16, 72, 136, 0, sorted(np.random.default_rng(12).choice(144, size=130, replace=False).tolist())),  # undivided
+])
+def test_rows_beyond_the_own_gemm_limit(case, tune):
+    """More rows than the library's own GEMM serves go to the GEMM library, with its standard and with tuned kernels."""
+    assert len(case[9]) * case[5] > kvs.KV_RECOMPUTE_OWN_GEMM_ROWS
+    run_case(*case, seed=59, tune=tune)
+
+
 def test_own_gemm_kernel_at_every_size(monkeypatch):
-    """Without the GEMM library (switched off through the environment) the projections of the
-    816-row case run on the library's own kernel as well: same bars."""
+    """Without the GEMM library (switched off through the environment) the 816-row case gives the same; 2080 rows, which
+    would otherwise go to that library: test_gpu_recompute_gemm."""
     monkeypatch.setenv("KVSWITCH_OWN_GEMM", "1")
     run_case(1, 8, 8, 128, 2048, 16, 1024, 2816, 0,
              sorted(np.random.default_rng(7).choice(128, size=51, replace=False).tolist()), seed=43)
