@@ -60,6 +60,41 @@ def test_huge_logit_in_a_short_run(D, hot_token):
           oracle.score_chunks(os_, q.numpy(), kv.numpy(), oracle.NORM_NONE))
 
 
+def longest_runs_bytes(g, R, longest):
+    rows, tiles = (R + 31) // 32 * 32, g.N // 32
+    runs = (tiles + longest - 1) // longest
+    least = 4 * g.L * g.Hq * rows * (tiles + g.N // min(g.T, 32) + 3 * runs)
+    return (least + 255) // 256 * 256
+
+
+@pytest.mark.parametrize("T", [8, 16, 32])
+@pytest.mark.parametrize("D", [64, 128, 256])
+@pytest.mark.parametrize("n_valid", [2048, 2015, 1983, 1951])
+def test_long_runs_of_the_shared_kernel(D, T, n_valid):
+    """63, 62, 61 and 60 tiles of one run below the causal diagonal, so that the loop over pairs of tiles turns many
+    times and ends in each of its ways; six row blocks per kv head: a wavefront (at head_dim 256 two) without work.  The
+    workspace holds the longest runs only, or these heads would be scored in runs of four tiles."""
+    g = synth.Geometry(1, 1, 6, D, 2048, T, 64)
+    ks, os_ = both_shapes(g)
+    kv = synth.make_kv(g, 43, "cpu", 1, 4.0)
+    q = (synth.make_q(g, 43, 32).float() * 6).to(torch.float16)
+    want = oracle.score_chunks_valid(os_, q.numpy(), kv.numpy(), n_valid, oracle.NORM_VISIBLE)
+    kv[:, :, :, n_valid:] = float("nan")
+    check(score_with(ks, q, kv, n_valid, longest_runs_bytes(g, 32, 64)), want)
+
+
+@pytest.mark.parametrize("D,T", [(64, 8), (64, 16), (128, 8), (256, 8), (256, 16), (256, 32)])
+@pytest.mark.parametrize("hot_token", [1000, 1980])
+def test_huge_logit_late_in_a_long_run(D, T, hot_token):
+    g = synth.Geometry(1, 1, 6, D, 2048, T, 64)
+    ks, os_ = both_shapes(g)
+    kv = (synth.make_kv(g, 47, "cpu").float() * 0.05).to(torch.float16)
+    kv[0, 0, 0, hot_token] = 20.0
+    q = torch.full((1, 6, 32, D), 2.0, dtype=torch.float16)
+    check(score_with(ks, q, kv, g.N, longest_runs_bytes(g, 32, 64)),
+          oracle.score_chunks(os_, q.numpy(), kv.numpy(), oracle.NORM_VISIBLE))
+
+
 @pytest.mark.parametrize("geom,R,longest", [
     ((1, 1, 4, 128, 2048, 16, 64), 32, 64),
     ((1, 1, 1, 64, 2048, 16, 64), 32, 8),
@@ -69,10 +104,7 @@ def test_workspace_that_holds_the_longest_runs_only(geom, R, longest):
     than these need is refused."""
     g = synth.Geometry(*geom)
     ks, os_ = both_shapes(g)
-    rows, tiles = (R + 31) // 32 * 32, g.N // 32
-    runs = (tiles + longest - 1) // longest
-    least = 4 * g.L * g.Hq * rows * (tiles + g.N // min(g.T, 32) + 3 * runs)
-    least = (least + 255) // 256 * 256
+    least = longest_runs_bytes(g, R, longest)
     assert least < kvs.kv_score_workspace_bytes(ks, R)
     kv = synth.make_kv(g, 67, "cpu", 1, 4.0)
     q = (synth.make_q(g, 67, R).float() * 6).to(torch.float16)
