@@ -353,7 +353,9 @@ __global__ __launch_bounds__(256, 2) void score_tiles_shared_kernel(const _Float
     const int run = blockIdx.x;
     const int tile_begin = run * g.run_len;
     if (tile_begin >= g.n_tiles) return;             // whole workgroup
+    // tiles of the run; those from real_end on are padding only: no row sees them
     const int tile_end = min(tile_begin + g.run_len, g.n_tiles);
+    const int real_end = min(tile_end, max((g.Nv + 31) / 32, tile_begin));
     const int rg = blockIdx.y * g.rg_per_wg + wave;
     const bool active = wave < g.rg_per_wg && rg < g.n_rg;
     const int l = blockIdx.z / g.Hkv, kvh = blockIdx.z % g.Hkv;
@@ -447,10 +449,6 @@ __global__ __launch_bounds__(256, 2) void score_tiles_shared_kernel(const _Float
             if (more) fetch(st, t + TS, to);
             if (active) {
                 for (int j = 0; j < TS && t + j < to; ++j) {
-                    if ((t + j) * 32 >= g.Nv) {         // padding only: no row sees it
-                        padding_tile(t + j);
-                        continue;
-                    }
                     v16f_t a[NRBW];
                     logits(a, buf, j);
 #pragma unroll
@@ -699,9 +697,13 @@ __global__ __launch_bounds__(256, 2) void score_tiles_shared_kernel(const _Float
     }
     for (int pass = dirty ? 0 : 1; pass < 2; ++pass) {
         const int from = pass == 0 ? tile_begin : fast_end;
-        const int to = pass == 0 ? fast_end : tile_end;
+        const int to = pass == 0 ? fast_end : real_end;
         if (from < to) general_pass(from, to);
     }
+    // (not in the general pass: a branch there keeps the compiler from overlapping its tiles, 170 tiles of three row
+    // blocks per kv head 89 instead of 81 us)
+    if (active)
+        for (int t = real_end; t < tile_end; ++t) padding_tile(t);
     if (active) {
 #pragma unroll
         for (int u = 0; u < NRBW; ++u) {
