@@ -353,9 +353,13 @@ __global__ __launch_bounds__(256, 2) void score_tiles_shared_kernel(const _Float
     const int run = blockIdx.x;
     const int tile_begin = run * g.run_len;
     if (tile_begin >= g.n_tiles) return;             // whole workgroup
-    // tiles of the run; those from real_end on are padding only: no row sees them
+    // tiles of the run; those from real_end on are padding only: no row sees them.  They are filled behind the general
+    // pass: a branch in its loop keeps the compiler from overlapping its tiles (170 tiles of three row blocks per kv head
+    // 89 instead of 81 us).  At head_dim 256 the branch is there all the same: the loop behind costs the fast pass eight
+    // more spilled registers (T 32: 5 %), and every tile below the diagonal goes through that pass.
+    constexpr bool kPaddingInPass = D == 256;
     const int tile_end = min(tile_begin + g.run_len, g.n_tiles);
-    const int real_end = min(tile_end, max((g.Nv + 31) / 32, tile_begin));
+    const int real_end = kPaddingInPass ? tile_end : min(tile_end, max((g.Nv + 31) / 32, tile_begin));
     const int rg = blockIdx.y * g.rg_per_wg + wave;
     const bool active = wave < g.rg_per_wg && rg < g.n_rg;
     const int l = blockIdx.z / g.Hkv, kvh = blockIdx.z % g.Hkv;
@@ -449,6 +453,10 @@ __global__ __launch_bounds__(256, 2) void score_tiles_shared_kernel(const _Float
             if (more) fetch(st, t + TS, to);
             if (active) {
                 for (int j = 0; j < TS && t + j < to; ++j) {
+                    if (kPaddingInPass && (t + j) * 32 >= g.Nv) {
+                        padding_tile(t + j);
+                        continue;
+                    }
                     v16f_t a[NRBW];
                     logits(a, buf, j);
 #pragma unroll
@@ -700,8 +708,6 @@ __global__ __launch_bounds__(256, 2) void score_tiles_shared_kernel(const _Float
         const int to = pass == 0 ? fast_end : real_end;
         if (from < to) general_pass(from, to);
     }
-    // (not in the general pass: a branch there keeps the compiler from overlapping its tiles, 170 tiles of three row
-    // blocks per kv head 89 instead of 81 us)
     if (active)
         for (int t = real_end; t < tile_end; ++t) padding_tile(t);
     if (active) {
