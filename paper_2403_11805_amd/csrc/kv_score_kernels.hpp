@@ -953,24 +953,25 @@ __global__ __launch_bounds__(256, 8) void score_combine_kernel(ScoreGeom g, Scor
     const int sbt_shift = __builtin_ctz(static_cast<unsigned>(sb_per_tile));
     __shared__ uint32_t fast_bits[kCombineMaxBlocks * kCombineMaxRuns / 32];
     const int bits_pitch = (g.n_runs + 63) / 64 * 2;         // words per row block
-    // one run per lane, the wavefront's 64 answers collected by a ballot (loads side by side, not in turn); a wavefront
-    // asks for four such rows of 64 runs at a time, blocks after one another (in turn they cost 8 heads of 256 rows 21
-    // instead of 13 us)
-    const int n64 = bits_pitch / 2;
-    for (int i0 = tid >> 6 << 2; i0 < g.RB * n64; i0 += 16) {
+    // One run per lane, the wavefront's 64 answers collected by a ballot.  A wavefront asks for two row blocks x 128 runs
+    // at a time, blocks and runs dealt out to the four (block after block in turn costs 8 heads of 256 rows 21 instead of
+    // 13 us).
+    const int across = g.RB == 1 ? 1 : (g.RB == 2 ? 2 : 4), wave = tid >> 6;     // wavefronts side by side on blocks
+    const int rb0 = wave & (across - 1), t_wave = (wave / across) * 128 + (tid & 63);
+    for (int t0 = 0; t0 < g.n_runs; t0 += 512 / across) {
         float v[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int i = min(i0 + u, g.RB * n64 - 1), rb = i / n64, t = (i - rb * n64) * 64 + (tid & 63);
-            const float x = mf[static_cast<int64_t>(min(t, g.n_runs - 1)) * g.rows_p + rb * 32];      // its first row exists
-            v[u] = t < g.n_runs ? x : __builtin_nanf("");
+            const int rb = min(rb0 + across * (u >> 1), g.RB - 1), t = t0 + t_wave + 64 * (u & 1);
+            v[u] = mf[static_cast<int64_t>(min(t, g.n_runs - 1)) * g.rows_p + rb * 32];      // a block's first row exists
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const uint64_t ok = __ballot(v[u] == v[u]);
-            if ((tid & 63) == 0 && i0 + u < g.RB * n64) {
-                fast_bits[2 * (i0 + u)] = static_cast<uint32_t>(ok);
-                fast_bits[2 * (i0 + u) + 1] = static_cast<uint32_t>(ok >> 32);
+            const int rb = rb0 + across * (u >> 1), t = t0 + t_wave + 64 * (u & 1);
+            const uint64_t ok = __ballot(t < g.n_runs && v[u] == v[u]);
+            if ((tid & 63) == 0 && rb < g.RB && t < g.n_runs) {
+                fast_bits[rb * bits_pitch + (t >> 5)] = static_cast<uint32_t>(ok);
+                fast_bits[rb * bits_pitch + (t >> 5) + 1] = static_cast<uint32_t>(ok >> 32);
             }
         }
     }

@@ -159,3 +159,18 @@ def test_static_array_gives_the_same_bits():
     torch.cuda.synchronize()
     want_cm, want_d = gpu_score(ks, q, kv, oracle.NORM_VISIBLE)
     assert np.array_equal(cm.cpu().numpy(), want_cm) and np.array_equal(d.cpu().numpy(), want_d)
+
+
+@pytest.mark.parametrize("R", [16, 64, 96, 160])
+def test_many_runs_and_row_blocks(R):
+    """256 runs of four tiles and one, two, three and five row blocks per head; the rows of one block of the second head
+    meet a key far above their run's reference."""
+    g = synth.Geometry(1, 1, 4, 64, 32768, 16, 64)
+    ks, os_ = both_shapes(g)
+    kv = (synth.make_kv(g, 53, "cpu").float() * 0.5).to(torch.float16)
+    kv[0, 0, 0, 20007] = 20.0
+    q = (synth.make_q(g, 53, R).float() * 6).to(torch.float16)
+    q -= q.float().mean(-1, keepdim=True).to(torch.float16)       # hardly anything to the hot key
+    q[0, 1, max(R - 32, 0):] = 2.0
+    check(gpu_score(ks, q.to(DEV), kv.to(DEV), oracle.NORM_VISIBLE),
+          oracle.score_chunks(os_, q.numpy(), kv.numpy(), oracle.NORM_VISIBLE))
