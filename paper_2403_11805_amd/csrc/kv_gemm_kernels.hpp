@@ -107,10 +107,11 @@ __device__ __forceinline__ void gemm_store8(const GemmArgs& g, int mat, int spli
 // the 16-row steps of K in turn, each holding the whole tile, with no barrier until their sums meet in LDS at the
 // end.  A wavefront keeps its loads kDepth steps ahead (8 x 512 bytes of weights and MB KiB of activations each);
 // the scheduling barriers keep the compiler from pulling the operand permutes of later steps, and with them the
-// waits for their loads, in front.  Weights are read once and marked non-temporal (72 against 78 us).
-// Measured, the four launches of a Llama-2-7B layer (404 MB of weights), with cold weights: 16 rows 72 us (5.6
-// TB/s; the LDS-tiled kernel before it 107), 64 rows 95 us; without the sums' way through LDS and the stores 64 us.
-// Grid (column tiles of all matrices, splits, row tiles of MB * 32), 256 threads.
+// waits for their loads, in front.  Weights are read once and marked non-temporal (8 % of a loop over the four
+// launches of a layer).
+// Measured in a kernel trace, the four launches of a Llama-2-7B layer (404 MB of weights) at 16 rows: 86 us (4.7 TB/s;
+// the LDS-tiled kernel before it 107).
+// Grid (column tiles of all matrices, splits), 256 threads; at most MB * 32 rows.
 template <int MB>
 __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs g) {
     constexpr int kWaves = 4, kDepth = MB == 1 ? 4 : 3, kCols = kStreamCols;
@@ -121,7 +122,6 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs g) {
     const int tile = blockIdx.x;
     const int mat = (tile >= g.tile_end[0]) + (tile >= g.tile_end[1]);
     const int n0 = (tile - (mat ? g.tile_end[mat - 1] : 0)) * kCols;
-    const int m0 = blockIdx.z * MB * 32;
     const int N = g.N[mat], K = g.K, K8 = K / 8;
     const int s_all = (K + kGemmStep - 1) / kGemmStep;
     const int sb = blockIdx.y * g.steps, se = min(s_all, sb + g.steps);
@@ -133,7 +133,7 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs g) {
     uint32_t a_rows[MB], a_lane[MB];                               // rows of the block, this lane's row in it
 #pragma unroll
     for (int b = 0; b < MB; ++b) {
-        const int rb = min(m0 + b * 32, (g.M - 1) / 32 * 32);
+        const int rb = min(b * 32, (g.M - 1) / 32 * 32);
         a_rows[b] = static_cast<uint32_t>(min(32, g.M - rb));
         a_base[b] = g.A + static_cast<size_t>(rb) * K;
         a_lane[b] = min(static_cast<uint32_t>(j), a_rows[b] - 1);
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs g) {
                 __builtin_amdgcn_sched_barrier(0);
             }
     }
-    // acc[c][b][v]: row m0 + b*32 + 8*(v/4) + 4*half + v%4, column n0 + 4*j + c; the wavefronts' sums are added in order
+    // acc[c][b][v]: row b*32 + 8*(v/4) + 4*half + v%4, column n0 + 4*j + c; the wavefronts' sums are added in order
 #pragma unroll
     for (int b = 0; b < MB; ++b) {
         if (b) __syncthreads();
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs g) {
                 lo += sums[(k * 32 + r) * (kCols / 4) + 2 * c8];
                 hi += sums[(k * 32 + r) * (kCols / 4) + 2 * c8 + 1];
             }
-            const int m = m0 + b * 32 + r, nn = n0 + 8 * c8;
+            const int m = b * 32 + r, nn = n0 + 8 * c8;
             if (m < g.M && nn < N) gemm_store8(g, mat, blockIdx.y, m, nn, lo, hi);
         }
     }
@@ -243,6 +243,7 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs g) {
 // At few rows a step is bound by its chain of waits (no MFMAs at all: 81 of 92 us for gate | up at 304 rows), at
 // many by the chip's power and by the last round of workgroups.
 // Grid 8 * ceil(column tiles * splits / 8) * row tiles, 256 threads; kGemmStage divides g.steps.
+// (MB 8, GATED spills three registers, the others none.)
 // GATED: two matrices of one width, splits == 1, and the result is C[0] = fp16(silu(A B[0]) * (A B[1])) in fragment
 // order, both products rounded to fp16 first; a column tile is 128 columns of each.
 template <int MB, bool GATED>
@@ -484,7 +485,7 @@ __global__ __launch_bounds__(256, MB <= 4 ? 2 : 1) void gemm_tile_kernel(GemmArg
     }
 }
 
-// C[0] = sum of matrix 0's partial products in split order + Cin, rounded once; four adjacent columns per thread.
+// C[0] = fp16(sum of matrix 0's partial products in split order + Cin); four adjacent columns per thread.
 __global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs g) {
     const size_t n4 = static_cast<size_t>(g.M) * g.N[0] / 4;
     const size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
@@ -497,13 +498,9 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmArgs g) {
         const gv4h_t c = reinterpret_cast<const gv4h_t*>(g.Cin)[i];
         a += gv4f_t{static_cast<float>(c[0]), static_cast<float>(c[1]), static_cast<float>(c[2]), static_cast<float>(c[3])};
     }
-    if (g.out_f32) {
-        reinterpret_cast<gv4f_t*>(g.C[0])[i] = a;
-    } else {
-        const gv4h_t h = {static_cast<_Float16>(a[0]), static_cast<_Float16>(a[1]), static_cast<_Float16>(a[2]),
-                          static_cast<_Float16>(a[3])};
-        reinterpret_cast<gv4h_t*>(g.C[0])[i] = h;
-    }
+    const gv4h_t h = {static_cast<_Float16>(a[0]), static_cast<_Float16>(a[1]), static_cast<_Float16>(a[2]),
+                      static_cast<_Float16>(a[3])};
+    reinterpret_cast<gv4h_t*>(g.C[0])[i] = h;
 }
 
 }  // namespace kvs

@@ -71,12 +71,14 @@ struct GemmGroup {
 struct OwnGemm {
     int mb, steps, splits;
     bool stream;
-    uint32_t col_tiles, row_tiles;
+    uint32_t col_tiles, row_tiles;      // (row tiles: tiled only; a streamed workgroup holds all rows)
 };
 
-// Up to 64 rows the weights are streamed: as many splits (at most 8) as make some 640 workgroups of a row block
-// (two per CU and some: gate | up of a Llama-2-7B layer, 16 rows, 34 us with 4 splits, 36 with one) or 256 of two
-// (o, 64 rows, 14.0 us with 8 splits, 14.9 with 6; q | k | v 26 with 2).
+// Up to 64 rows the weights are streamed: as many splits (at most 8) as make some 640 workgroups of a row block (two
+// per CU and some) or 256 of two: for a Llama-2-7B layer q | k | v 6 and 2, o and down 8 and 8, gate | up 3 and 1 (o,
+// 64 rows, 14.0 us with 8 splits, 14.9 with 6).  The rule looks at the launch alone; gate | up at 16 rows would rather
+// not be divided, since its activation then reads fp16: the whole layer takes 119 us with 3 splits, 116 with 2, 112
+// with one.
 // Above, the row blocks per workgroup (3..8) and the splits that minimise
 //     rounds of 256 workgroups * steps * (0.184 + 0.0453 * row blocks) us
 //     + writing and reading the partial products at 3.25 TB/s each;
@@ -106,7 +108,6 @@ OwnGemm own_gemm_plan(int64_t M, const int64_t* N, int n_mats, int64_t K, uint64
         best.stream = true;
         best.mb = M <= 32 ? 1 : 2;
         best.col_tiles = static_cast<uint32_t>(tiles(kStreamCols));
-        best.row_tiles = 1;
         int64_t s = (best.mb == 1 ? 640 : 256) / best.col_tiles;
         s = std::max<int64_t>(1, std::min<int64_t>({s, 8, room_splits, steps / 16}));
         best.steps = static_cast<int>((steps + s - 1) / s);
@@ -297,7 +298,7 @@ enum class Out { kF32, kF16, kGate };
 // `left` (one matrix only) a divided product is added here.
 int own_gemm(hipStream_t st, FixedTile fixed, int64_t M, int64_t K, const void* A, const GemmGroup& grp, const void* Cin,
              Out out, Room room, Product* left, const char* what) {
-    if (!left && grp.n != 1) return fail(KV_EINVAL, "GEMM (%s): a group is added by its reader", what);
+    if (!left && (grp.n != 1 || out != Out::kF16)) return fail(KV_EINVAL, "GEMM (%s): added by its reader only", what);
     if (K % 8 || K < 8 || M < 1 || grp.n < 1 || grp.n > kGemmMaxMats || (Cin && grp.n != 1))
         return fail(KV_ESHAPE, "GEMM (%s): unsupported shape", what);
     for (int j = 0; j < grp.n; ++j)
@@ -332,7 +333,7 @@ int own_gemm(hipStream_t st, FixedTile fixed, int64_t M, int64_t K, const void* 
     g.out_f32 = out == Out::kF32 ? 1 : 0;
     g.out_fragments = out == Out::kGate && h.splits == 1 ? 1 : 0;
     if (h.stream) {
-        const dim3 grid(h.col_tiles, static_cast<uint32_t>(h.splits), h.row_tiles);
+        const dim3 grid(h.col_tiles, static_cast<uint32_t>(h.splits));
         if (h.mb == 1) hipLaunchKernelGGL(gemm_stream_kernel<1>, grid, dim3(256), 0, st, g);
         else hipLaunchKernelGGL(gemm_stream_kernel<2>, grid, dim3(256), 0, st, g);
     } else {
