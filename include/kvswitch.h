@@ -491,16 +491,23 @@ typedef struct {
 } kv_layer_weights_t;
 
 /* Handle of the recompute path.  The projections of up to KV_RECOMPUTE_OWN_GEMM_ROWS recomputed
- * tokens (what a plan of Eq. 4 recomputes beside a Load) run on the library's own MFMA GEMM,
- * which is the faster one there (per Llama-2-7B layer 0.18 ms at 128 tokens, 0.27 at 304, 0.34 at 512;
- * at 2048 0.96 against 1.21 ms with rocBLAS); larger ones are handed
+ * tokens (what a plan of Eq. 4 recomputes beside a Load) run on the library's own MFMA GEMM:
+ * a Llama-2-7B layer takes 0.18 ms at 128 tokens, 0.27 at 304, 0.34 at 512.  Larger ones are handed
  * to rocBLAS, which is loaded on creation if it is installed (the handle then owns that
- * library's handle, whose device workspace lives until kv_recompute_destroy).  Without
- * rocBLAS, or with KVSWITCH_OWN_GEMM=1 in the environment at creation, every size runs on the
+ * library's handle, whose device workspace lives until kv_recompute_destroy).  The limit goes by
+ * tokens alone.  Measured at 1024 and 2048 tokens, us a layer, own kernels / rocBLAS with its
+ * standard kernels / with those kv_recompute_tune picks (d_model, kv heads of 128, d_ff):
+ *   1024,  8,  2816    126 /  158 /  158     197 /  213 /  205
+ *   2048, 16,  5632    232 /  286 /  280     377 /  404 /  387
+ *   4096, 32, 11008    571 /  620 /  625     992 / 1219 / 1027
+ *   4096,  8, 14336    599 /  636 /  635    1040 / 1061 / 1060
+ *   5120, 40, 13824    807 /  910 /  882    1520 / 1538 / 1457
+ *   8192,  8, 28672   1793 / 1816 / 1795    3303 / 3309 / 3305
+ * Without rocBLAS, or with KVSWITCH_OWN_GEMM=1 in the environment at creation, every size runs on the
  * library's own kernel (1.1 PFLOP/s at 4096 rows).  KVSWITCH_GEMM_TILE=<row blocks 3..8>,<splits 1..16>
- * in the environment at creation takes the choice of that kernel's launch shape above 64 rows from the library, as
- * far as K and the workspace allow the splits (tests and measurements; another value fails).  NULL on
- * failure (kv_last_error has the text).  One handle serves one stream at a time. */
+ * in the environment at creation takes the choice of that kernel's launch shape above 64 rows from the
+ * library, as far as K and the workspace allow the splits (tests and measurements; another value
+ * fails).  NULL on failure (kv_last_error has the text).  One handle serves one stream at a time. */
 #define KV_RECOMPUTE_OWN_GEMM_ROWS 2048
 typedef struct kv_recompute kv_recompute_t;
 kv_recompute_t* kv_recompute_create(void);
@@ -512,16 +519,16 @@ uint64_t kv_recompute_workspace_bytes(const kv_shape_t* shape, const kv_layer_di
 
 /* Optional, once per (handle, n_missing): choose the GEMM library's kernels for the five projection
  * shapes of a block over n_missing chunks by timing them on the caller's weights and workspace
- * (Sec. 3.3 i profiles the recompute delay before planning; for a few hundred tokens the
- * library's default kernels are far from the best it has).  Every listed kernel is timed back to
- * back; the standard choice and the best few are timed again with cold weights, the other
- * projections of the block running in between as in a layer; the winner is used by later
- * kv_recompute_layer calls with the same n_missing if it beats the standard choice by more than
- * 5 %.  Unlike every other device call this one SYNCHRONISES `stream`, takes of the order of a
- * second, and overwrites the workspace.  n_improved (may be NULL) receives the number of shapes
- * that got another kernel; 0 and KV_OK if the library cannot list its kernels, and where the
- * projections do not go to the GEMM library at all (few tokens, see above, or no rocBLAS): nothing is
- * then timed.  Results are the same up to the summation order inside a GEMM. */
+ * (Sec. 3.3 i profiles the recompute delay before planning; the library's default kernels are not
+ * always the best it has).  Every listed kernel is timed back to back; the standard choice and the
+ * best few are timed again with cold weights, the other projections of the block running in between
+ * as in a layer; the winner is used by later kv_recompute_layer calls with the same n_missing if it
+ * beats the standard choice by more than 5 %.  Unlike every other device call this one SYNCHRONISES
+ * `stream`, takes of the order of a second, and overwrites the workspace.  n_improved (may be NULL)
+ * receives the number of shapes that got another kernel; 0 and KV_OK if the library cannot list its
+ * kernels, and where the projections do not go to the GEMM library at all (up to
+ * KV_RECOMPUTE_OWN_GEMM_ROWS tokens, or no rocBLAS): nothing is then timed.  Results are the same up
+ * to the summation order inside a GEMM. */
 int32_t kv_recompute_tune(kv_recompute_t* rc, const kv_shape_t* shape, const kv_layer_dims_t* dims,
                           const kv_layer_weights_t* weights, int32_t n_missing, void* workspace,
                           uint64_t workspace_bytes, void* stream, int32_t* n_improved);
@@ -532,7 +539,8 @@ int32_t kv_recompute_tune(kv_recompute_t* rc, const kv_shape_t* shape, const kv_
  *   x_in   dev fp16 [n_missing * chunk_tokens][d_model]: the layer inputs of these tokens,
  *          chunk by chunk in the order of chunk_idx_dev;
  *   kv     dev fp16 cache; the K and V planes of `layer` must hold every resident chunk that
- *          lies before the last recomputed token; the recomputed chunks' entries are written;
+ *          lies before the last recomputed token (what lies behind it may be anything, NaN
+ *          included); the recomputed chunks' entries are written;
  *   x_out  dev fp16, same shape as x_in: the layer outputs (may not alias x_in);
  *   workspace dev, >= kv_recompute_workspace_bytes(), 256-byte aligned, contents scratch.
  * Enqueues on `stream` and returns; nothing is launched if a host argument is invalid. */

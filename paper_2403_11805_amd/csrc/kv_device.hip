@@ -623,7 +623,7 @@ static int32_t score_launch(const kv_shape_t* shape, const ScoreGeom& g, int nrb
                            g.L * g.Hq, n_chunks_h, inv_norm_h, g.T, g.Nv);
         return launch_status("score_density_kernel launch");
     }
-    if (g.rg_per_wg > 1) {          // several row groups per kv head: two row blocks per wavefront
+    if (g.rg_per_wg > 1) {          // several row groups per kv head: K shared through LDS
         if (D == 64) KV_SCORE_SHARED(64);
         else if (D == 128) KV_SCORE_SHARED(128);
         else KV_SCORE_SHARED(256);

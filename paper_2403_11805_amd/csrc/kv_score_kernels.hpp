@@ -305,9 +305,10 @@ __global__ __launch_bounds__(256) void score_tiles_kernel(const _Float16* __rest
 // Variant for grouped-query attention: the 2-4 wavefronts of a workgroup hold
 // the row blocks (shared_blocks_per_wave each) of different query heads that read the SAME kv head,
 // so K is fetched once per workgroup (fully coalesced, 16 bytes per thread and
-// access), staged in LDS (two buffers of two tiles; the 16-byte pieces of a row
-// are permuted by its row number so that the operand reads are bank-conflict
-// free) and read from there by every wavefront: one barrier per 64 tokens.
+// access), staged in LDS (two buffers of two tiles, of one at head_dim 256; the
+// 16-byte pieces of a row are permuted by its row number so that the operand
+// reads are bank-conflict free) and read from there by every wavefront: one
+// barrier per stage.
 //
 // A run is processed in up to three passes over its tiles:
 //  - the fast pass over the tiles below the causal diagonal.  The row references
@@ -316,19 +317,24 @@ __global__ __launch_bounds__(256) void score_tiles_kernel(const _Float16* __rest
 //    ahead, into the register the tile at hand has just used, and inside a
 //    wavefront the MFMAs of a tile are interleaved, instruction by instruction,
 //    with the softmax partials of the tile before it (two accumulator sets used in
-//    turn).  Bound by those partials: per block of 32 x 32 some 52 VALU
-//    instructions and 16 exponentials at a quarter of their rate, 420 cycles
-//    against 256 of MFMA (32 layers x 32 heads on 8 kv heads, 32768 tokens, R = 64:
-//    751 us per call; 797 with the order left to sched_group_barrier patterns and
-//    the loads behind branches, where the compiler drains them);
+//    turn).  What bounds it (counters, 32 layers x 32 heads on 8 kv heads of 128,
+//    32768 tokens, R = 64, 2048 blocks of 32 x 32 per SIMD): 513 cycles a block, in
+//    256 of which the matrix pipe is busy, in 322 the VALU (16 exponentials at a
+//    quarter of the rate and some 47 other instructions), in 165 both and in 100
+//    neither.  The chip's power does the rest: called again and again the kernel takes
+//    the same 1.05 M cycles, but its clock falls from 1.76 to 1.4 GHz, 622 to 757 us.
+//    (The whole call 751 us; 797 with the order left to sched_group_barrier patterns
+//    and the loads behind branches, where the compiler drains them - 1.29 M cycles in
+//    all, but at 1.92 GHz);
 //  - the general pass (tile_epilogue) over the tiles that reach the diagonal;
 //  - the general pass over the whole fast range again if some sum left the safe
-//    range there (workgroup-wide decision), or instead of the fast pass if a
-//    wavefront holds only one row block.
+//    range there (workgroup-wide decision), or instead of the fast pass if the row
+//    blocks of a kv head do not fill every wavefront's two.
 //
 // Row blocks per wavefront: two, but one at head_dim 256, where the two query blocks alone would hold 128
 // registers: 171 spilled, and 4.4 us went by per tile of 32 tokens (18 layers x 8 heads x 4096 tokens, the same
-// run lengths: 82.2 -> 33.3 us per call; one wavefront per SIMD with 512 registers instead: 45.2 us).
+// run lengths: 82.2 -> 33.3 us per call; one wavefront per SIMD with 512 registers instead: 45.2 us).  With one
+// 11 to 13 still spill there.
 constexpr int shared_blocks_per_wave(int head_dim) { return head_dim == 256 ? 1 : 2; }
 
 template <int D, int SBT>
