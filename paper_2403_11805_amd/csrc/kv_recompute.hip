@@ -76,11 +76,13 @@ struct OwnGemm {
     uint32_t col_tiles, row_tiles;      // (row tiles: tiled only; a streamed workgroup holds all rows)
 };
 
-// Up to 64 rows the weights are streamed: as many splits (at most 8) as make some 640 workgroups of a row block (two
-// per CU and some) or 256 of two: for a Llama-2-7B layer q | k | v 6 and 2, o and down 8 and 8, gate | up 3 and 1 (o,
-// 64 rows, 14.0 us with 8 splits, 14.9 with 6).  The rule looks at the launch alone; gate | up at 16 rows would rather
-// not be divided, since its activation then reads fp16: the whole layer takes 119 us with 3 splits, 116 with 2, 112
-// with one.
+// Up to 64 rows the weights are streamed: as many splits (at most 8) as keep every workgroup resident at once, 512 of a
+// row block (two per CU) or 256 of two: for a Llama-2-7B layer q | k | v 5 and 2, o and down 8 and 8, gate | up 2 and 1.
+// A few workgroups more than that are a second round, in which the chip is nearly empty: with 640 wanted (q | k | v
+// 576, gate | up 516) the layer took 122.5 us at 16 rows and 138.6 at 32, with 512 115.6 and 132.4; 384: 117.5 and
+// 133.8; d_model 2048, d_ff 5632, 16 rows 69.9 / 66.9 (384: 67.1); d_model 3072, d_ff 8192 90.0 / 85.8 (87.5); up to 16
+// splits of o and down 119.2.  Undivided gate | up with the activation in its epilogue saves a launch, but one
+// workgroup per CU streams only half as fast as two (d_ff 11008 117.3 us, 8192 114 instead of 104).
 // Above, the row blocks per workgroup (3..8) and the splits that minimise
 //     rounds of 256 workgroups * steps * (0.184 + 0.0453 * row blocks) us
 //     + writing and reading the partial products at 3.25 TB/s each;
@@ -110,7 +112,7 @@ OwnGemm own_gemm_plan(int64_t M, const int64_t* N, int n_mats, int64_t K, uint64
         best.stream = true;
         best.mb = M <= 32 ? 1 : 2;
         best.col_tiles = static_cast<uint32_t>(tiles(kStreamCols));
-        int64_t s = (best.mb == 1 ? 640 : 256) / best.col_tiles;
+        int64_t s = (best.mb == 1 ? 512 : 256) / best.col_tiles;
         s = std::max<int64_t>(1, std::min<int64_t>({s, 8, room_splits, steps / 16}));
         best.steps = static_cast<int>((steps + s - 1) / s);
         best.splits = static_cast<int>((steps + best.steps - 1) / best.steps);
