@@ -164,20 +164,28 @@ uint64_t partials_reserve(int64_t M, const int64_t* N, int n_mats, int64_t K) {
     return splits > 1 ? static_cast<uint64_t>(splits) * M * n_sum * 4u : 0u;
 }
 
+uint64_t attention_share_bytes(const kv_shape_t& s, int64_t M) {
+    return static_cast<uint64_t>(M) * s.n_q_heads * (s.head_dim + 2) * 4;
+}
+
+// One or two (row block, query head) pairs per kv head go to the kernel whose wavefronts share a pair: a layer of 32 rows
+// 132.4 -> 129.6 us (32 heads, d_model 4096), 48 rows 137 -> 133.7, 64 rows 145 -> 142.8, 32 heads on 16 kv heads, 32 rows
+// 114.5 -> 107.8.  With three pairs reading the keys three times costs more than the idle wavefront (80 rows 153 -> 159).
+bool few_pairs(int64_t pairs) { return pairs <= 2; }
+
 // With few recomputed rows the attention kernel has too few workgroups to fill 256 CUs: the key ranges are then
 // divided (at least four key tiles per share over the whole cache), as far as there is room for the shares, until
 // some 512 workgroups exist (two per CU; 768 cost more in partial results than they gain: 512 rows, 32 heads, 356
 // against 344 us per layer).  More than eight shares only where eight do not make 256 workgroups: 128 rows, 32 heads
-// 182 us with 8, 188 with 16, 190 with 4; 4 kv heads, 16 rows 52 us with 16, 53 with 8.
-uint64_t attention_share_bytes(const kv_shape_t& s, int64_t M) {
-    return static_cast<uint64_t>(M) * s.n_q_heads * (s.head_dim + 2) * 4;
-}
+// 182 us with 8, 188 with 16, 190 with 4; 4 kv heads, 16 rows 52 us with 16, 53 with 8.  Where the wavefronts of a
+// workgroup share a pair, 256 workgroups of at least eight tiles do (512: the same at one pair, 3 us more at two).
 int attention_splits(const kv_shape_t& s, int64_t M, uint64_t room) {
     const int64_t pairs = static_cast<int64_t>(s.n_q_heads / s.n_kv_heads) * ((M + 31) / 32);
-    const int64_t base = (pairs + kAttnWaves - 1) / kAttnWaves * s.n_kv_heads;
-    int64_t splits = 512 / base;
+    const bool few = few_pairs(pairs);
+    const int64_t base = (few ? pairs : (pairs + kAttnWaves - 1) / kAttnWaves) * s.n_kv_heads;
+    int64_t splits = (few ? 256 : 512) / base;
     if (splits > 8) splits = std::max<int64_t>(8, std::min<int64_t>(kMaxSplits, 256 / base));
-    splits = std::min<int64_t>(splits, (s.n_tokens + 31) / 32 / 4);
+    splits = std::min<int64_t>(splits, (s.n_tokens + 31) / 32 / (few ? 8 : 4));
     splits = std::min<int64_t>(splits, static_cast<int64_t>(room / attention_share_bytes(s, M)));
     return static_cast<int>(std::max<int64_t>(splits, 1));
 }
@@ -678,35 +686,32 @@ int32_t kv_recompute_layer(kv_recompute_t* rc, const kv_shape_t* shape, const kv
     g.pairs = (Hq / Hkv) * g.n_rb;
     g.fragments = own ? 1 : 0;
     g.scale_log2e = static_cast<float>(1.4426950408889634 / std::sqrt(static_cast<double>(D)));
-    const uint32_t pair_blocks = static_cast<uint32_t>((g.pairs + kAttnWaves - 1) / kAttnWaves);
+    const bool few = few_pairs(g.pairs);
     // (the shares of a divided attention lie behind its output)
     const Room shares = room(p.x1, p.total);
     const int splits = attention_splits(s, M, shares.bytes);
-    if (splits > 1) {
-        const int64_t pairs_all = M * Hq;
-        float* part_o = reinterpret_cast<float*>(shares.at);
-        float* part_ml = part_o + static_cast<int64_t>(splits) * pairs_all * D;
-        const dim3 agrid(pair_blocks, static_cast<uint32_t>(Hkv), static_cast<uint32_t>(splits));
-        if (D == 64) {
-            hipLaunchKernelGGL((recompute_attention_kernel<64, true>), agrid, dim3(64 * kAttnWaves), 0, st, q16,
-                               k_plane, v_plane, chunk_idx_dev, attn, g, part_o, part_ml);
-            hipLaunchKernelGGL(attention_combine_kernel<64>, dim3(static_cast<uint32_t>((pairs_all * 16 + 255) / 256)),
-                               dim3(256), 0, st, part_o, part_ml, attn, pairs_all, splits, Hq, g.fragments);
-        } else {
-            hipLaunchKernelGGL((recompute_attention_kernel<128, true>), agrid, dim3(64 * kAttnWaves), 0, st, q16,
-                               k_plane, v_plane, chunk_idx_dev, attn, g, part_o, part_ml);
-            hipLaunchKernelGGL(attention_combine_kernel<128>, dim3(static_cast<uint32_t>((pairs_all * 32 + 255) / 256)),
-                               dim3(256), 0, st, part_o, part_ml, attn, pairs_all, splits, Hq, g.fragments);
-        }
-    } else {
-        const dim3 agrid(pair_blocks, static_cast<uint32_t>(Hkv));
-        if (D == 64)
-            hipLaunchKernelGGL((recompute_attention_kernel<64, false>), agrid, dim3(64 * kAttnWaves), 0, st, q16,
-                               k_plane, v_plane, chunk_idx_dev, attn, g, nullptr, nullptr);
-        else
-            hipLaunchKernelGGL((recompute_attention_kernel<128, false>), agrid, dim3(64 * kAttnWaves), 0, st, q16,
-                               k_plane, v_plane, chunk_idx_dev, attn, g, nullptr, nullptr);
-    }
+    const int64_t pairs_all = M * Hq;
+    float* part_o = splits > 1 ? reinterpret_cast<float*>(shares.at) : nullptr;
+    float* part_ml = splits > 1 ? part_o + static_cast<int64_t>(splits) * pairs_all * D : nullptr;
+    const dim3 agrid(static_cast<uint32_t>(few ? g.pairs : (g.pairs + kAttnWaves - 1) / kAttnWaves), static_cast<uint32_t>(Hkv),
+                     static_cast<uint32_t>(splits));
+#define KV_ATTENTION(KERNEL, DD, SPLIT)                                                                          \
+    hipLaunchKernelGGL((KERNEL<DD, SPLIT>), agrid, dim3(64 * kAttnWaves), 0, st, q16, k_plane, v_plane, chunk_idx_dev, \
+                       attn, g, part_o, part_ml)
+#define KV_ATTENTION_D(DD)                                                                                       \
+    do {                                                                                                         \
+        if (few && splits > 1) KV_ATTENTION(recompute_attention_few_kernel, DD, true);                           \
+        else if (few) KV_ATTENTION(recompute_attention_few_kernel, DD, false);                                   \
+        else if (splits > 1) KV_ATTENTION(recompute_attention_kernel, DD, true);                                 \
+        else KV_ATTENTION(recompute_attention_kernel, DD, false);                                                \
+        if (splits > 1)                                                                                          \
+            hipLaunchKernelGGL(attention_combine_kernel<DD>, dim3(static_cast<uint32_t>((pairs_all * (DD / 4) + 255) / 256)), \
+                               dim3(256), 0, st, part_o, part_ml, attn, pairs_all, splits, Hq, g.fragments);     \
+    } while (0)
+    if (D == 64) KV_ATTENTION_D(64);
+    else KV_ATTENTION_D(128);
+#undef KV_ATTENTION_D
+#undef KV_ATTENTION
     // 4. output projection + residual, feed-forward + residual
     const GemmGroup og = {1, {dims->d_model}, {w->wo}, {x1}};
     // (free but for xn and x1, which the norm writes while it adds the partial products)

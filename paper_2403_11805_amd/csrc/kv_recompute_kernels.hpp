@@ -262,6 +262,85 @@ struct AttnGeom {
     float scale_log2e;
 };
 
+constexpr float kRefSlack = 8.0f;
+// Piece c of row r of a K tile in LDS sits at c ^ attn_swz(r); a token row of a V tile there takes attn_v_pitch halves.
+template <int D>
+__device__ __forceinline__ int attn_swz(int r) { return D == 64 ? (r >> 1) & 7 : r & 15; }
+constexpr int attn_v_pitch(int D) { return D + 16; }
+
+// One tile of 32 tokens from `t * 32` on, in LDS, against a wavefront's 32 query rows: folds it into the outputs o_acc,
+// the references m_run and the denominators l_run.
+template <int D>
+__device__ __forceinline__ void attention_tile(const ru4_t* ktile, const _Float16* vt, const rv8h_t (&qreg)[D / 16],
+                                               rv16f_t (&o_acc)[D / 32], float& m_run, float& l_run, int t, int min_pos,
+                                               int pos, float scale_log2e, int lane) {
+    constexpr int KS = D / 16, DB = D / 32, kRowPieces = D / 8, kVPitch = attn_v_pitch(D);
+    const int lrow = lane & 31, half = lane >> 5;
+    rv8h_t kreg[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+        kreg[ks] = __builtin_bit_cast(rv8h_t, ktile[lrow * kRowPieces + ((2 * ks + half) ^ attn_swz<D>(lrow))]);
+    rv16f_t acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(kreg[ks], qreg[ks], acc, 0, 0, 0);
+    // acc[v]: token t*32 + 8*(v/4) + 4*half + v%4 against this lane's query row
+    // maxima on the raw logits (the scale is positive), the scale folded into the exponent
+    const bool masked = t * 32 + 31 > min_pos;     // wave-uniform
+    float mloc = -INFINITY;
+    if (masked) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int tk = t * 32 + 8 * (v / 4) + 4 * half + (v % 4);
+            if (tk > pos) acc[v] = -INFINITY;
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) mloc = fmaxf(mloc, acc[v]);
+    // The reference of a row moves only when some row of the wavefront has left it by more than 2^8: until
+    // then its probabilities are up to 2^8 instead of 1, which costs fp16 no precision, and the 64
+    // accumulators are not touched.
+    const float m_tile = xhalf_max(mloc) * scale_log2e;
+    if (__any(m_tile > m_run + kRefSlack)) {        // wave-uniform
+        const float m_new = fmaxf(m_run, m_tile);
+        const float alpha = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.0f : m_new));
+        m_run = m_new;
+        l_run *= alpha;
+#pragma unroll
+        for (int b = 0; b < DB; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) o_acc[b][v] *= alpha;
+    }
+    const float m_safe = (m_run == -INFINITY) ? 0.0f : m_run;
+    float psum = 0.0f;
+    rv8h_t pb[2];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v], scale_log2e, -m_safe));
+        psum += pv;
+        pb[v / 8][v % 8] = static_cast<_Float16>(pv);
+    }
+    l_run += xhalf_sum(psum);
+    // contraction slot (half, e) of step st holds token 16*st + 4*half + e (e < 4) or
+    // 16*st + 8 + 4*half + e - 4: the order of acc[8*st .. 8*st+7] on the P side
+#pragma unroll
+    for (int b = 0; b < DB; ++b) {
+        // this lane's piece of the block of its 16-lane group: token row (lane % 16) / 4, channels
+        // 32 b + 16 (group % 2) + 4 (lane % 4) ..; the read returns channel 32 b + lane % 32
+        const _Float16* vblk = &vt[((lane & 15) >> 2) * kVPitch + 32 * b + 16 * ((lane >> 4) & 1) + 4 * (lane & 3)];
+#pragma unroll
+        for (int st = 0; st < 2; ++st) {
+            const rv4s_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                (__attribute__((address_space(3))) rv4s_t*)(vblk + (16 * st + 4 * half) * kVPitch));
+            const rv4s_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                (__attribute__((address_space(3))) rv4s_t*)(vblk + (16 * st + 8 + 4 * half) * kVPitch));
+            const rv4h_t lo_h = __builtin_bit_cast(rv4h_t, lo), hi_h = __builtin_bit_cast(rv4h_t, hi);
+            const rv8h_t a = {lo_h[0], lo_h[1], lo_h[2], lo_h[3], hi_h[0], hi_h[1], hi_h[2], hi_h[3]};
+            o_acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, pb[st], o_acc[b], 0, 0, 0);
+        }
+    }
+}
+
 // Causal attention of the recomputed queries over the recovered K/V of one layer.
 // A wavefront owns one (block of 32 query rows, query head) pair: S^T = K_tile Q^T
 // with mfma_f32_32x32x16_f16 (a lane owns one query row and 16 of the tile's 32
@@ -289,7 +368,6 @@ constexpr int kMaxSplits = 16;     // workgroups that may share the key range of
 // gridDim.z workgroups; each writes the unnormalised output, running maximum and denominator of its
 // share (part_o [split][row][head][D], part_ml [split][row][head][2], binary32) and
 // attention_combine_kernel merges the shares in a fixed order.
-constexpr float kRefSlack = 8.0f;
 template <int D, bool SPLIT>
 __global__ __launch_bounds__(64 * kAttnWaves, 2) void recompute_attention_kernel(
     const _Float16* __restrict__ q16, const _Float16* __restrict__ k_plane,
@@ -307,9 +385,8 @@ __global__ __launch_bounds__(64 * kAttnWaves, 2) void recompute_attention_kernel
     // the LDS transpose read (ds_read_b64_tr_b16): the 16 lanes of a group hand in the sixteen
     // 8-byte pieces of a 4-token x 16-channel block, row by row, and lane i receives the four
     // tokens of channel i.  The padding puts the four token rows of a block on different banks.
-    constexpr int kVPitch = D + 16;
+    constexpr int kVPitch = attn_v_pitch(D);
     __shared__ __align__(16) _Float16 vt[2][32 * kVPitch];
-    auto swz = [](int r) __attribute__((always_inline)) { return D == 64 ? (r >> 1) & 7 : r & 15; };
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -381,7 +458,7 @@ __global__ __launch_bounds__(64 * kAttnWaves, 2) void recompute_attention_kernel
         for (int i = 0; i < kPer; ++i) {
             const int p = min(i * kThreads + tid, kTilePieces - 1);
             const int r = p / kRowPieces, c = p % kRowPieces;
-            ktile[buf][r * kRowPieces + (c ^ swz(r))] = kst[set][i];
+            ktile[buf][r * kRowPieces + (c ^ attn_swz<D>(r))] = kst[set][i];
             *reinterpret_cast<ru4_t*>(&vt[buf][r * kVPitch + c * 8]) = vst[set][i];
         }
     };
@@ -395,69 +472,7 @@ __global__ __launch_bounds__(64 * kAttnWaves, 2) void recompute_attention_kernel
     // into the other register set) goes to the other buffer and its set fetches tile t + 3
     auto step = [&](int t, int buf) __attribute__((always_inline)) {
         if (t < n_tiles && t * 32 <= max_pos) {     // wave-uniform
-            rv8h_t kreg[KS];
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                kreg[ks] = __builtin_bit_cast(rv8h_t, ktile[buf][lrow * kRowPieces + ((2 * ks + half) ^ swz(lrow))]);
-            rv16f_t acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(kreg[ks], qreg[ks], acc, 0, 0, 0);
-            // acc[v]: token t*32 + 8*(v/4) + 4*half + v%4 against this lane's query row
-            // maxima on the raw logits (the scale is positive), the scale folded into the exponent
-            const bool masked = t * 32 + 31 > min_pos;     // wave-uniform
-            float mloc = -INFINITY;
-            if (masked) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int tk = t * 32 + 8 * (v / 4) + 4 * half + (v % 4);
-                    if (tk > pos) acc[v] = -INFINITY;
-                }
-            }
-#pragma unroll
-            for (int v = 0; v < 16; ++v) mloc = fmaxf(mloc, acc[v]);
-            // The reference of a row moves only when some row of the wavefront has left it by more than 2^8: until
-            // then its probabilities are up to 2^8 instead of 1, which costs fp16 no precision, and the 64
-            // accumulators are not touched.
-            const float m_tile = xhalf_max(mloc) * g.scale_log2e;
-            if (__any(m_tile > m_run + kRefSlack)) {        // wave-uniform
-                const float m_new = fmaxf(m_run, m_tile);
-                const float alpha = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.0f : m_new));
-                m_run = m_new;
-                l_run *= alpha;
-#pragma unroll
-                for (int b = 0; b < DB; ++b)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) o_acc[b][v] *= alpha;
-            }
-            const float m_safe = (m_run == -INFINITY) ? 0.0f : m_run;
-            float psum = 0.0f;
-            rv8h_t pb[2];
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v], g.scale_log2e, -m_safe));
-                psum += pv;
-                pb[v / 8][v % 8] = static_cast<_Float16>(pv);
-            }
-            l_run += xhalf_sum(psum);
-            // contraction slot (half, e) of step st holds token 16*st + 4*half + e (e < 4) or
-            // 16*st + 8 + 4*half + e - 4: the order of acc[8*st .. 8*st+7] on the P side
-#pragma unroll
-            for (int b = 0; b < DB; ++b) {
-                // this lane's piece of the block of its 16-lane group: token row (lane % 16) / 4, channels
-                // 32 b + 16 (group % 2) + 4 (lane % 4) ..; the read returns channel 32 b + lane % 32
-                const _Float16* vblk = &vt[buf][((lane & 15) >> 2) * kVPitch + 32 * b + 16 * ((lane >> 4) & 1) + 4 * (lane & 3)];
-#pragma unroll
-                for (int st = 0; st < 2; ++st) {
-                    const rv4s_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                        (__attribute__((address_space(3))) rv4s_t*)(vblk + (16 * st + 4 * half) * kVPitch));
-                    const rv4s_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                        (__attribute__((address_space(3))) rv4s_t*)(vblk + (16 * st + 8 + 4 * half) * kVPitch));
-                    const rv4h_t lo_h = __builtin_bit_cast(rv4h_t, lo), hi_h = __builtin_bit_cast(rv4h_t, hi);
-                    const rv8h_t a = {lo_h[0], lo_h[1], lo_h[2], lo_h[3], hi_h[0], hi_h[1], hi_h[2], hi_h[3]};
-                    o_acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, pb[st], o_acc[b], 0, 0, 0);
-                }
-            }
+            attention_tile<D>(ktile[buf], vt[buf], qreg, o_acc, m_run, l_run, t, min_pos, pos, g.scale_log2e, lane);
         }
         // (both unconditional, beyond the last tile with that tile again: behind a branch the compiler waits for every
         // load in flight before it parks)
@@ -510,6 +525,151 @@ __global__ __launch_bounds__(64 * kAttnWaves, 2) void recompute_attention_kernel
                 for (int k = 0; k < 4; ++k) o4[k] = static_cast<_Float16>(o_acc[b][4 * j + k] * inv);
                 *reinterpret_cast<rv4h_t*>(dst + (4 * b + j) * piece + 4 * half) = o4;
             }
+    }
+}
+
+// The same with few (row block, query head) pairs per kv head, where most wavefronts of the kernel above would have no
+// pair of their own: the four wavefronts of a workgroup share ONE pair and take the key tiles of the workgroup's share in
+// turn, each through a tile of LDS of its own and with no barrier before their outputs meet at the end.
+// Grid (pairs, kv heads, shares).
+template <int D, bool SPLIT>
+__global__ __launch_bounds__(64 * kAttnWaves, 2) void recompute_attention_few_kernel(
+    const _Float16* __restrict__ q16, const _Float16* __restrict__ k_plane,
+    const _Float16* __restrict__ v_plane, const int32_t* __restrict__ chunk_idx,
+    _Float16* __restrict__ out, AttnGeom g, float* __restrict__ part_o, float* __restrict__ part_ml) {
+    constexpr int KS = D / 16;
+    constexpr int DB = D / 32;
+    constexpr int kRowPieces = D / 8;
+    constexpr int kVPitch = attn_v_pitch(D);
+    constexpr int kPer = 32 * kRowPieces / 64;      // 16-byte pieces of a K (or V) tile per lane
+    constexpr int kVPieces = kVPitch / 8;
+    static_assert(32 * (kRowPieces + kVPieces) >= 8 * D, "a wavefront's tile holds its outputs");
+    __shared__ ru4_t tile_lds[kAttnWaves][32 * (kRowPieces + kVPieces)];
+    __shared__ float ml_lds[kAttnWaves][2][32];
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int lrow = lane & 31, half = lane >> 5;
+    // (the workgroups of a kv head on one XCD, the longest key ranges first: as above)
+    const int gx = static_cast<int>(gridDim.x), nz = SPLIT ? static_cast<int>(gridDim.z) : 1;
+    int kvh = blockIdx.y, bxi = blockIdx.x, share = SPLIT ? static_cast<int>(blockIdx.z) : 0;
+    if (g.Hkv % 8 == 0) {
+        const int lin = (share * g.Hkv + static_cast<int>(blockIdx.y)) * gx + static_cast<int>(blockIdx.x);
+        const int per_xcd = lin >> 3, nth = per_xcd / (gx * nz), in = per_xcd - nth * (gx * nz);
+        kvh = (lin & 7) + 8 * nth;
+        share = in / gx;
+        bxi = in - share * gx;
+    }
+    const int per = g.Hq / g.Hkv;
+    const int pair = gx - 1 - bxi;
+    const int head = kvh * per + pair % per, rb = pair / per;
+    const int m = rb * 32 + lrow;
+    const bool ok = m < g.M;
+    const int pos = ok ? global_position(chunk_idx, g.T, m) : -1;
+    const int min_pos = global_position(chunk_idx, g.T, rb * 32);
+    const int max_pos = global_position(chunk_idx, g.T, min(rb * 32 + 31, g.M - 1));
+    const int all_tiles = max_pos / 32 + 1, per_share = (all_tiles + nz - 1) / nz;
+    const int t_first = share * per_share, n_tiles = min(all_tiles, t_first + per_share);
+
+    const ru4_t* kbase = reinterpret_cast<const ru4_t*>(k_plane + static_cast<int64_t>(kvh) * g.N * D);
+    const ru4_t* vbase = reinterpret_cast<const ru4_t*>(v_plane + static_cast<int64_t>(kvh) * g.N * D);
+    ru4_t kst[kPer], vst[kPer];
+    auto fetch = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int p = i * 64 + lane;
+            const int token = min(t * 32 + p / kRowPieces, max_pos);     // (what lies behind the last row may be anything)
+            const int64_t src = static_cast<int64_t>(token) * kRowPieces + p % kRowPieces;
+            kst[i] = kbase[src];
+            vst[i] = vbase[src];
+        }
+    };
+    ru4_t* ktile = tile_lds[wave];
+    _Float16* vt = reinterpret_cast<_Float16*>(ktile + 32 * kRowPieces);
+    auto park = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int p = i * 64 + lane, r = p / kRowPieces, c = p % kRowPieces;
+            ktile[r * kRowPieces + (c ^ attn_swz<D>(r))] = kst[i];
+            *reinterpret_cast<ru4_t*>(vt + r * kVPitch + c * 8) = vst[i];
+        }
+    };
+    auto in_order = [] {                            // LDS accesses of this wavefront on either side stay there
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    fetch(min(t_first + wave, all_tiles - 1));
+    rv8h_t qreg[KS];
+    {
+        const _Float16* qp = q16 + (static_cast<int64_t>(ok ? m : 0) * g.Hq + head) * D + half * 8;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            rv8h_t v = {0, 0, 0, 0, 0, 0, 0, 0};
+            if (ok) v = *reinterpret_cast<const rv8h_t*>(qp + ks * 16);
+            qreg[ks] = v;
+        }
+    }
+    rv16f_t o_acc[DB];
+#pragma unroll
+    for (int b = 0; b < DB; ++b) o_acc[b] = rv16f_t{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    float m_run = -INFINITY, l_run = 0.0f;
+    for (int t = t_first + wave; t < n_tiles; t += kAttnWaves) {
+        park();
+        fetch(min(t + kAttnWaves, n_tiles - 1));
+        in_order();
+        attention_tile<D>(ktile, vt, qreg, o_acc, m_run, l_run, t, min_pos, pos, g.scale_log2e, lane);
+        in_order();
+    }
+    // the four outputs against one reference per row, added in the order of the wavefronts
+    if (half == 0) {
+        ml_lds[wave][0][lrow] = m_run;
+        ml_lds[wave][1][lrow] = l_run;
+    }
+    __syncthreads();
+    float m_all = -INFINITY, l_all = 0.0f;
+#pragma unroll
+    for (int k = 0; k < kAttnWaves; ++k) m_all = fmaxf(m_all, ml_lds[k][0][lrow]);
+#pragma unroll
+    for (int k = 0; k < kAttnWaves; ++k) {
+        const float mk = ml_lds[k][0][lrow];
+        l_all += mk == -INFINITY ? 0.0f : ml_lds[k][1][lrow] * __builtin_amdgcn_exp2f(mk - m_all);
+    }
+    const float f = m_run == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m_run - m_all);
+    rv4f_t* mine = reinterpret_cast<rv4f_t*>(ktile);
+#pragma unroll
+    for (int b = 0; b < DB; ++b)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            mine[(b * 4 + j) * 64 + lane] = rv4f_t{o_acc[b][4 * j], o_acc[b][4 * j + 1], o_acc[b][4 * j + 2], o_acc[b][4 * j + 3]} * f;
+    __syncthreads();
+    // wavefront b finishes channels 32 b ..: 32 b + 8 j + 4 half .. of this lane's row
+    if (wave >= DB || !ok) return;
+    rv4f_t o[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        o[j] = reinterpret_cast<const rv4f_t*>(tile_lds[0])[(wave * 4 + j) * 64 + lane];
+#pragma unroll
+        for (int k = 1; k < kAttnWaves; ++k) o[j] += reinterpret_cast<const rv4f_t*>(tile_lds[k])[(wave * 4 + j) * 64 + lane];
+    }
+    if constexpr (SPLIT) {
+        const int64_t row = (static_cast<int64_t>(share) * g.M + m) * g.Hq + head;
+        if (wave == 0 && half == 0) {
+            part_ml[row * 2] = m_all;
+            part_ml[row * 2 + 1] = l_all;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) *reinterpret_cast<rv4f_t*>(part_o + row * D + 32 * wave + 8 * j + 4 * half) = o[j];
+    } else {
+        const float inv = 1.0f / l_all;             // a row sees at least its own token
+        const int piece = g.fragments ? min(32, g.M - rb * 32) * 8 : 8;
+        _Float16* dst = out + (g.fragments ? fragment_at(m, head * D, g.M, g.Hq * D) : (static_cast<int64_t>(m) * g.Hq + head) * D);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            rv4h_t o4;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) o4[k] = static_cast<_Float16>(o[j][k] * inv);
+            *reinterpret_cast<rv4h_t*>(dst + (4 * wave + j) * piece + 4 * half) = o4;
+        }
     }
 }
 

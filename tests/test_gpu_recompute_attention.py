@@ -77,3 +77,36 @@ def test_nothing_behind_the_last_token_is_used(Hkv, Hq, D, N, T, missing):
     rc.close()
     err = close(y.cpu().numpy(), y_ref, 1e-2, 1e-2, "layer output")
     assert err < 3e-3
+
+
+@pytest.mark.parametrize("Hkv,Hq,D,N,T,missing", [
+    (1, 1, 64, 64, 8, [2]),                      # one pair of 8 rows, one tile: three wavefronts have none
+    (1, 1, 128, 96, 8, [0, 3, 11]),              # one pair of 24 rows, three tiles, undivided
+    (1, 1, 128, 1024, 16, [63]),                 # one pair, divided in four: eight tiles a share, two a wavefront
+    (16, 16, 64, 512, 8, [10]),                  # divided, kv heads dealt to the XCDs; the row sees less than a share
+    (2, 2, 128, 1184, 16, [1, 30, 73]),          # two pairs: 32 rows and 16; 37 tiles, shares of 10, the last one short
+    (8, 16, 128, 224, 8, [0, 27]),               # two heads on a kv head, undivided, rows at both ends
+    (3, 3, 64, 2048, 16, [5, 64, 100, 127]),     # two pairs of 32 rows, kv heads in plain order
+])
+def test_few_pairs_share_a_workgroup(Hkv, Hq, D, N, T, missing):
+    """One or two (row block, head) pairs per kv head: the wavefronts of a workgroup take the key tiles of one pair in
+    turn, some of them none, and their outputs are merged."""
+    d_model, d_ff = 256, 512
+    shape = kvs.Shape(1, Hkv, Hq, D, N, T, 64)
+    dims_o = orc.LayerDims(d_model, Hq, Hkv, D, d_ff)
+    dims = binding.LayerDims(d_model, d_ff, dims_o.rope_base, dims_o.rms_eps)
+    w = synth.make_layer_weights(d_model, Hq, Hkv, D, d_ff, 97)
+    kv = (synth.make_kv(synth.Geometry(1, Hkv, Hq, D, N, T, 64), 97, "cpu").float() * 0.2).to(torch.float16)
+    rows = np.concatenate([np.arange(c * T, (c + 1) * T) for c in missing])
+    x = synth.make_hidden(len(rows), d_model, 97)
+    k_ref, v_ref = kv[0, 0].numpy().copy(), kv[0, 1].numpy().copy()
+    y_ref = orc.recompute_layer(x.numpy(), missing, T, k_ref, v_ref, {k: v.numpy() for k, v in w.items()}, dims_o)
+    y = torch.full((len(rows), d_model), float("nan"), dtype=torch.float16, device=DEV)
+    ws = torch.empty(kvs.kv_recompute_workspace_bytes(shape, dims, len(missing)), dtype=torch.uint8, device=DEV)
+    rc = kvs.Recompute()
+    rc.layer(shape, dims, {k: v.to(DEV) for k, v in w.items()}, 0,
+             torch.tensor(missing, dtype=torch.int32, device=DEV), x.to(DEV), kv.to(DEV), y, ws)
+    torch.cuda.synchronize()
+    rc.close()
+    err = close(y.cpu().numpy(), y_ref, 1e-2, 1e-2, "layer output")
+    assert err < 3e-3
