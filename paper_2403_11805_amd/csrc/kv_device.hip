@@ -436,23 +436,38 @@ static int score_geom(const kv_shape_t* shape, int32_t n_queries, int32_t n_vali
 }
 
 // A run is what one wavefront (one workgroup where K is shared through LDS) walks alone, so few heads over a
-// short context leave most of the chip idle with the longest runs: they are halved until the launch has some
-// 256 workgroups where K is shared, 128 where a workgroup holds four runs side by side - but not below four
-// (two) tiles, since a run opens with two trips to memory (query rows, first tile) before it has anything to
-// do.  Measured (us per call, longest runs / 128 / 256 / 512 workgroups wanted):
-//   18 layers, 8 heads on one kv head of 256, 4096 tokens, R 32     49.9 / 36.6 / 33.3 / 33.8
-//   4 layers, 16 heads on 4 kv heads of 128, 8192 tokens, R 64      55.0 / 37.8 / 29.1 / 31.6
-//   28 layers, 28 heads on 4 kv heads of 128, 4096 tokens, R 64     104.9 / 105.0 / 105.2 / 114.7
-//   18 layers, one head of 256, 4096 tokens, R 32 (four runs side by side)   28.0 / 20.8 / 23.7 / 23.7
-//   6 layers, 12 heads of 256, 2048 tokens, R 32 (likewise)                  28.5 / 28.5 / 32.4 / 29.7
-static void shorten_runs(ScoreGeom* g) {
+// short context leave most of the chip idle with the longest runs.
+// K shared: where the longest runs make fewer than 256 workgroups, a head gets as many runs as keep all workgroups
+// resident at once (one workgroup more is a second round), 512 (two per CU) or, where those would be shorter than 20 tiles -
+// a run opens with two trips to memory, query rows and first tile, before it has anything to do -, 256.  At head_dim 256
+// a tile takes twice as long and 512 are better down to ten tiles.  Not below eight tiles, and no power of two: runs
+// that many KiB apart meet in the same memory channels.  Measured (us per call; halving the longest runs until 256
+// workgroups exist, as before / 256 / 512 workgroups / the next power of two; tiles of a run):
+//   18 layers, 8 heads on one kv head of 256, 4096 tokens, R 23   33.8 (16) / 34.7 (19) / 29.8 (10) / 33.4 (8)
+//   the same, R 64                                                47.0 (32) / 50.3 (40) / 43.4 (19) / 47.9 (16)
+//   4 layers, 16 heads on 4 kv heads of 128, 8192 tokens, R 64    30.8 (16) / 24.3 (18) / 28.6 (9) / 32.3 (8)
+//   20 layers, 40 heads on 5 of 128, 3200 tokens, R 9             52.1 (32) / 53 (50) / 45.4 (20) / 45.6 (16)
+//   12 layers, 20 heads on 5 of 64, 2048 tokens, R 17             22.5 (16) / 21.1 (18) / 20.7 (9) / 22.8 (8)
+//   8 layers, 32 heads on 8 of 128, 4096 tokens, R 64             41.8 (32) / 40.4 (40) / 41.5 (18) / 47.3 (16)
+//   4 layers, 8 heads on one of 64, 32768 tokens, R 64            35.7 (32) / 32.6 (40) / 36.2 (18) / 37.9 (16)
+// Four runs side by side in a workgroup: halved until 128 workgroups exist, but not below two tiles (us per call, longest
+// runs / 128 / 256 / 512 wanted):
+//   18 layers, one head of 256, 4096 tokens, R 32                 28.0 / 20.8 / 23.7 / 23.7
+//   6 layers, 12 heads of 256, 2048 tokens, R 32                  28.5 / 28.5 / 32.4 / 29.7
+static void shorten_runs(ScoreGeom* g, int head_dim) {
     const bool shared = g->tile_par == 1;
     const int64_t heads = static_cast<int64_t>(g->L) * g->Hkv * ((g->n_rg + g->rg_per_wg - 1) / g->rg_per_wg);
-    const int64_t wanted = shared ? 256 : 128;
-    const int min_run = shared ? 4 : 2;
     int run = shared ? 64 : 8;
     auto groups = [&] { return ((g->n_tiles + run - 1) / run + g->tile_par - 1) / g->tile_par * heads; };
-    while (run > min_run && groups() < wanted) run /= 2;
+    if (!shared) {
+        while (run > 2 && groups() < 128) run /= 2;
+    } else if (groups() < 256) {
+        auto tiles_of = [&](int64_t runs) { return static_cast<int>((g->n_tiles + runs - 1) / runs); };
+        run = tiles_of(512 / heads);
+        if (head_dim != 256 && run < 20) run = tiles_of(256 / heads);
+        run = std::min(std::max(run, 8), 64);
+        if (run < 64 && !(run & (run - 1))) ++run;
+    }
     if (run >= g->n_tiles) return;
     g->run_len = run;
     g->n_runs = (g->n_tiles + run - 1) / run;
@@ -484,14 +499,13 @@ static uint64_t score_head_lds_bytes(const ScoreGeom& g, int head_dim) {
 
 // The geometry to launch with, given `available` bytes of scratch.  Shorter runs need a little more (three floats
 // per row and run); a workspace that holds the longest runs only - one made for another shape - is served with
-// these, as long as it holds them.  How much more: the last halving starts from at most 255 workgroups of a run and up
-// to eight row blocks each (K shared), or from 127 of four runs and two row blocks, and it doubles the runs: 3 floats *
-// 510 * 256 rows = 1.5 MiB at the most.
+// these, as long as it holds them.  How much more: at most 512 workgroups of a run and up to eight row blocks each (K
+// shared), 3 floats * 512 * 256 rows = 1.5 MiB; or twice 127 of four runs and two row blocks, less.
 constexpr uint64_t kShortRunsExtraBytes = 2u << 20;
 static ScoreGeom fitted_runs(const ScoreGeom& g, int head_dim, uint64_t available) {
     if (score_head_lds_bytes(g, head_dim)) return g;
     ScoreGeom s = g;
-    shorten_runs(&s);
+    shorten_runs(&s, head_dim);
     return score_ws_bytes(s) <= available ? s : g;
 }
 

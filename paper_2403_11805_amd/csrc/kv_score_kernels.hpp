@@ -954,8 +954,9 @@ __global__ __launch_bounds__(256, 8) void score_combine_kernel(ScoreGeom g, Scor
     // one holds four blocks, otherwise eight)
     const float* mf = ws.m_fast + static_cast<int64_t>(lh) * g.n_runs * g.rows_p;
     const int first_tail_tile = (g.Nv - g.R + 1) / 32;
-    // run_len is a power of two whenever a head has more than one run; sb_per_tile is 1, 2 or 4
-    const int run_shift = g.n_runs > 1 ? __builtin_ctz(static_cast<unsigned>(g.run_len)) : 31;
+    // run of a tile: (tile + 1/2) / run_len lies at least 1 / (2 * 64) from any whole number, rounding moves it by less than
+    // 2^-22 of kCombineMaxRuns = 2^13 (a head of one run: the quotient is below 1); sb_per_tile is 1, 2 or 4
+    const float per_run = 1.0f / static_cast<float>(g.run_len), half_run = 0.5f * per_run;
     const int sbt_shift = __builtin_ctz(static_cast<unsigned>(sb_per_tile));
     __shared__ uint32_t fast_bits[kCombineMaxBlocks * kCombineMaxRuns / 32];
     const int bits_pitch = (g.n_runs + 63) / 64 * 2;         // words per row block
@@ -1000,7 +1001,7 @@ __global__ __launch_bounds__(256, 8) void score_combine_kernel(ScoreGeom g, Scor
                     const int c = min(c0 + u, n_chunks - 1);
                     const int sb = c * sb_per_chunk + k;
                     const int tile = sb >> sbt_shift;
-                    const int rn = tile >> run_shift;
+                    const int rn = static_cast<int>(__builtin_fmaf(static_cast<float>(tile), per_run, half_run));
                     // (a chunk's sub-block lies in one tile, the lane's four rows in one block)
                     const bool fast = tile < first_tail_tile && ((fast_bits[(rr >> 5) * bits_pitch + (rn >> 5)] >> (rn & 31)) & 1u);
                     mi[u] = *reinterpret_cast<const float4*>(fast ? mf + static_cast<int64_t>(rn) * g.rows_p + rr

@@ -174,3 +174,19 @@ def test_many_runs_and_row_blocks(R):
     q[0, 1, max(R - 32, 0):] = 2.0
     check(gpu_score(ks, q.to(DEV), kv.to(DEV), oracle.NORM_VISIBLE),
           oracle.score_chunks(os_, q.numpy(), kv.numpy(), oracle.NORM_VISIBLE))
+
+
+@pytest.mark.parametrize("geom,R,n_valid", [
+    ((18, 1, 8, 256, 1600, 16, 64), 23, 1589),   # 36 workgroups a run: runs of nine tiles, 50 tiles, the last run of five
+    ((20, 5, 20, 128, 1600, 32, 64), 9, 1600),   # 100: three runs of 25 tiles of 50 (two would be 50): 25 and 25
+    ((4, 4, 16, 128, 4096, 8, 64), 40, 4075),    # 16: runs of nine tiles instead of eight, 128 tiles, the last of two
+    ((1, 1, 6, 64, 2080, 16, 64), 32, 2017),     # one workgroup a run: nine tiles at least, the last run of two is padding
+])
+def test_runs_of_any_length(geom, R, n_valid):
+    """Runs whose length is no power of two: the combine kernel finds a tile's run by a product with 1 / length."""
+    ks, os_ = both_shapes(synth.Geometry(*geom))
+    kv = synth.make_kv(synth.Geometry(*geom), 71, "cpu", 1, 4.0)
+    q = (synth.make_q(synth.Geometry(*geom), 71, R).float() * 6).to(torch.float16)
+    want = oracle.score_chunks_valid(os_, q.numpy(), kv.numpy(), n_valid, oracle.NORM_VISIBLE)
+    kv[:, :, :, n_valid:] = float("nan")
+    check(score_with(ks, q, kv, n_valid, kvs.kv_score_workspace_bytes(ks, R)), want)
