@@ -595,6 +595,14 @@ int32_t kv_score_chunks_static(const kv_shape_t* shape, const void* q, int32_t n
                         density, stream);
 }
 
+// Where a workgroup holds all row blocks of a kv head, K is read once; from the size of the memory-side cache (256 MiB) on
+// nothing of it is there for the next call either, and it is read past the caches, which then keep the partials on their
+// way to the combine kernel: plain / past the caches, us per call called again and again,
+//   32 heads on 8 kv heads of 128, R 64, 32768 tokens: 4 layers (256 MiB) 108 / 105, 8 193 / 191, 16 376 / 368, 32 745 / 735
+//   32 layers, 32 on 8 of 128, 16384 tokens, R 32 315 / 295;  24 layers, 32 on 4 of 128, 16384, R 30 183 / 173
+//   22 layers, 48 on 12 of 128, 8288, R 3 164 / 158;  32 layers, 32 on 8 of 64, 16384, R 64 308 / 299
+//   below, the next call finds K in the cache: 4 layers of 16384 tokens (128 MiB) 59 / 63
+constexpr uint64_t kReadOnceBytes = 256u << 20;
 static int32_t score_launch(const kv_shape_t* shape, const ScoreGeom& g, int nrbw, const void* q, const void* kv,
                             void* workspace, float* chunk_mass, float* density, void* stream) {
     ScoreWs ws;
@@ -608,14 +616,17 @@ static int32_t score_launch(const kv_shape_t* shape, const ScoreGeom& g, int nrb
                     (g.n_rg + g.rg_per_wg - 1) / g.rg_per_wg, g.L * g.Hkv);
     const _Float16* qp = static_cast<const _Float16*>(q);
     const _Float16* kp = static_cast<const _Float16*>(kv);
+    const bool once = grid.y == 1 && static_cast<uint64_t>(g.L) * g.Hkv * g.N * shape->head_dim * 2u >= kReadOnceBytes;
+#define KV_SCORE_SHARED_T(DD, SBT)                                                                    \
+    do {                                                                                             \
+        if (once) hipLaunchKernelGGL((score_tiles_shared_kernel<DD, SBT, true>), grid, dim3(256), 0, st, qp, kp, g, ws); \
+        else hipLaunchKernelGGL((score_tiles_shared_kernel<DD, SBT, false>), grid, dim3(256), 0, st, qp, kp, g, ws); \
+    } while (0)
 #define KV_SCORE_SHARED(DD)                                                                           \
     do {                                                                                             \
-        if (g.sb_tokens == 32)                                                                       \
-            hipLaunchKernelGGL((score_tiles_shared_kernel<DD, 1>), grid, dim3(256), 0, st, qp, kp, g, ws); \
-        else if (g.sb_tokens == 16)                                                                  \
-            hipLaunchKernelGGL((score_tiles_shared_kernel<DD, 2>), grid, dim3(256), 0, st, qp, kp, g, ws); \
-        else                                                                                         \
-            hipLaunchKernelGGL((score_tiles_shared_kernel<DD, 4>), grid, dim3(256), 0, st, qp, kp, g, ws); \
+        if (g.sb_tokens == 32) KV_SCORE_SHARED_T(DD, 1);                                             \
+        else if (g.sb_tokens == 16) KV_SCORE_SHARED_T(DD, 2);                                        \
+        else KV_SCORE_SHARED_T(DD, 4);                                                               \
     } while (0)
 #define KV_SCORE_DIRECT(DD, NR) \
     hipLaunchKernelGGL((score_tiles_kernel<DD, NR>), grid, dim3(256), 0, st, qp, kp, g, ws)
@@ -648,6 +659,7 @@ static int32_t score_launch(const kv_shape_t* shape, const ScoreGeom& g, int nrb
     else if (nrbw == 1) KV_SCORE_DIRECT(256, 1);
     else KV_SCORE_DIRECT(256, 2);
 #undef KV_SCORE_SHARED
+#undef KV_SCORE_SHARED_T
 #undef KV_SCORE_DIRECT
     if (int rc = launch_status("score_tiles_kernel launch")) return rc;
     // 32 chunks per pass of a workgroup; a head's chunks are divided among several workgroups where the

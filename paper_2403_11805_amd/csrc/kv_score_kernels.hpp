@@ -331,13 +331,15 @@ __global__ __launch_bounds__(256) void score_tiles_kernel(const _Float16* __rest
 //    range there (workgroup-wide decision), or instead of the fast pass if the row
 //    blocks of a kv head do not fill every wavefront's two.
 //
+// ONCE: K is read past the caches (the host's rule).
+//
 // Row blocks per wavefront: two, but one at head_dim 256, where the two query blocks alone would hold 128
 // registers: 171 spilled, and 4.4 us went by per tile of 32 tokens (18 layers x 8 heads x 4096 tokens, the same
 // run lengths: 82.2 -> 33.3 us per call; one wavefront per SIMD with 512 registers instead: 45.2 us).  With one
 // 11 to 13 still spill there.
 constexpr int shared_blocks_per_wave(int head_dim) { return head_dim == 256 ? 1 : 2; }
 
-template <int D, int SBT>
+template <int D, int SBT, bool ONCE>
 __global__ __launch_bounds__(256, 2) void score_tiles_shared_kernel(const _Float16* __restrict__ q,
                                                                     const _Float16* __restrict__ kv,
                                                                     ScoreGeom g, ScoreWs ws) {
@@ -491,7 +493,7 @@ __global__ __launch_bounds__(256, 2) void score_tiles_shared_kernel(const _Float
         auto load_piece = [&](int set, int stage, int i) __attribute__((always_inline)) {
             const int tile = min(stage * TS + i * 256 / kTilePieces, n_fast - 1);
             st[set][i] = __builtin_bit_cast(su4_t, __builtin_amdgcn_raw_buffer_load_b128(
-                k_run, static_cast<uint32_t>(tid) * 16u, static_cast<uint32_t>(tile * kTilePieces + i * 256 % kTilePieces) * 16u, 0));
+                k_run, static_cast<uint32_t>(tid) * 16u, static_cast<uint32_t>(tile * kTilePieces + i * 256 % kTilePieces) * 16u, ONCE ? 2 : 0));
         };
         auto fetch_stage = [&](int set, int stage) __attribute__((always_inline)) {
 #pragma unroll

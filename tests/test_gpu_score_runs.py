@@ -190,3 +190,31 @@ def test_runs_of_any_length(geom, R, n_valid):
     want = oracle.score_chunks_valid(os_, q.numpy(), kv.numpy(), n_valid, oracle.NORM_VISIBLE)
     kv[:, :, :, n_valid:] = float("nan")
     check(score_with(ks, q, kv, n_valid, kvs.kv_score_workspace_bytes(ks, R)), want)
+
+
+@pytest.mark.parametrize("L,D,T", [(4, 64, 8), (4, 64, 16), (2, 128, 16), (2, 128, 32)])
+def test_keys_read_past_the_caches(L, D, T):
+    """256 MiB of keys, the least that is read past the caches, against a call per layer, which reads its share through
+    them: the same runs (256 workgroups of the longest in a layer), the same sums, the same bits."""
+    Hkv, Hq, N, R = 8, 24, 65536, 5
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(73)
+    kv = torch.empty((L, 2, Hkv, N, D), dtype=torch.float16, device=DEV)
+    for l in range(L):
+        kv[l] = torch.randn((2, Hkv, N, D), generator=gen, device=DEV)
+    q = torch.randn((L, Hq, R, D), generator=gen, device=DEV).half()
+    assert L * Hkv * N * D * 2 == 256 << 20
+
+    def masses(layers, qs, kvs_):
+        ks = kvs.Shape(layers, Hkv, Hq, D, N, T, 64)
+        cm = torch.full((layers, Hq, ks.n_chunks), float("nan"), dtype=torch.float32, device=DEV)
+        d = torch.zeros(ks.n_chunks, dtype=torch.float32, device=DEV)
+        ws = torch.full((kvs.kv_score_workspace_bytes(ks, R),), 0xff, dtype=torch.uint8, device=DEV)
+        kvs.kv_score_chunks(ks, qs, kvs_, oracle.NORM_VISIBLE, ws, cm, d)
+        torch.cuda.synchronize()
+        return cm
+
+    together = masses(L, q, kv)
+    assert torch.isfinite(together).all()
+    for l in range(L):
+        assert torch.equal(together[l], masses(1, q[l:l + 1].contiguous(), kv[l:l + 1].contiguous())[0])
