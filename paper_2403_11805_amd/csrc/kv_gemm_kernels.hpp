@@ -109,8 +109,8 @@ __device__ __forceinline__ void gemm_store8(const GemmArgs& g, int mat, int spli
 // the scheduling barriers keep the compiler from pulling the operand permutes of later steps, and with them the
 // waits for their loads, in front.  Weights are read once and marked non-temporal (8 % of a loop over the four
 // launches of a layer).
-// Measured in a kernel trace, the four launches of a Llama-2-7B layer (404 MB of weights) at 16 rows: 86 us (4.7 TB/s;
-// the LDS-tiled kernel before it 107).
+// Measured in a kernel trace, the four launches of a Llama-2-7B layer (404 MB of weights) at 16 rows: 82 us (4.9 TB/s;
+// 86 with the last few workgroups in a second round, the LDS-tiled kernel before it 107).
 // Grid (column tiles of all matrices, splits), 256 threads; at most MB * 32 rows.
 template <int MB>
 __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs g) {
@@ -240,8 +240,9 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs g) {
 // it 312), 512 rows 301 (348), 2048 rows 832 us = 1.00 PFLOP/s (the GEMM library's standard choice 1042).
 // Loading eight columns of two rows per lane and exchanging them between lanes changes nothing (269 and 267 us a
 // layer at 304 rows, 990 and 998 at 2048): the width of the weight loads is not what a step waits for.
-// At few rows a step is bound by its chain of waits (no MFMAs at all: 81 of 92 us for gate | up at 304 rows), at
-// many by the chip's power and by the last round of workgroups.
+// At few rows a step is bound by what the CU takes in: some 55 bytes per ns as soon as some loads miss L2, 52 KB for 64 of
+// K at five row blocks (no MFMAs at all: 81 of 92 us for gate | up at 304 rows); at many by the chip's power and by the
+// last round of workgroups.
 // Grid 8 * ceil(column tiles * splits / 8) * row tiles, 256 threads; kGemmStage divides g.steps.
 // (MB 8, GATED spills three registers, the others none.)
 // GATED: two matrices of one width, splits == 1, and the result is C[0] = fp16(silu(A B[0]) * (A B[1])) in fragment

@@ -34,10 +34,10 @@ def check(got, want):
     ((1, 1, 3, 256, 1056, 16, 64), 32, 1056),    # head_dim 256, three row blocks: one wavefront of four without work
     ((2, 1, 8, 256, 544, 8, 64), 23, 471),       # eight blocks in two workgroups, 17 tiles, the last two padding only
     ((1, 1, 2, 256, 256, 32, 256), 33, 97),      # two heads of two blocks; most of the cache is padding
-    ((1, 1, 4, 128, 160, 32, 64), 5, 160),       # 5 tiles: a run of four and one of one
+    ((1, 1, 4, 128, 160, 32, 64), 5, 160),       # 5 tiles: nothing to shorten
     ((1, 1, 4, 64, 128, 16, 64), 32, 128),       # 4 tiles: nothing to shorten
     ((3, 1, 1, 64, 96, 16, 64), 9, 70),          # four runs side by side, 3 tiles: runs of two and one, padding behind
-    ((200, 1, 4, 64, 256, 16, 64), 32, 250),     # enough heads: two runs of four tiles
+    ((200, 1, 4, 64, 256, 16, 64), 32, 250),     # 200 workgroups of one run of eight tiles
 ])
 def test_short_runs(geom, R, n_valid):
     ks, os_ = both_shapes(synth.Geometry(*geom))
@@ -73,7 +73,7 @@ def longest_runs_bytes(g, R, longest):
 def test_long_runs_of_the_shared_kernel(D, T, n_valid):
     """63, 62, 61 and 60 tiles of one run below the causal diagonal, so that the loop over pairs of tiles turns many
     times and ends in each of its ways; six row blocks per kv head: a wavefront (at head_dim 256 two) without work.  The
-    workspace holds the longest runs only, or these heads would be scored in runs of four tiles."""
+    workspace holds the longest runs only, or these heads would be scored in runs of nine tiles."""
     g = synth.Geometry(1, 1, 6, D, 2048, T, 64)
     ks, os_ = both_shapes(g)
     kv = synth.make_kv(g, 43, "cpu", 1, 4.0)
