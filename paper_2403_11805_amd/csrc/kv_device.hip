@@ -437,23 +437,74 @@ static int score_geom(const kv_shape_t* shape, int32_t n_queries, int32_t n_vali
 
 // A run is what one wavefront (one workgroup where K is shared through LDS) walks alone, so few heads over a
 // short context leave most of the chip idle with the longest runs.
-// K shared: where the longest runs make fewer than 256 workgroups, a head gets as many runs as keep all workgroups
-// resident at once (one workgroup more is a second round), 512 (two per CU) or, where those would be shorter than 20 tiles -
-// a run opens with two trips to memory, query rows and first tile, before it has anything to do -, 256.  At head_dim 256
-// a tile takes twice as long and 512 are better down to ten tiles.  Not below eight tiles, and no power of two: runs
-// that many KiB apart meet in the same memory channels.  Measured (us per call; halving the longest runs until 256
-// workgroups exist, as before / 256 / 512 workgroups / the next power of two; tiles of a run):
-//   18 layers, 8 heads on one kv head of 256, 4096 tokens, R 23   33.8 (16) / 34.7 (19) / 29.8 (10) / 33.4 (8)
-//   the same, R 64                                                47.0 (32) / 50.3 (40) / 43.4 (19) / 47.9 (16)
-//   4 layers, 16 heads on 4 kv heads of 128, 8192 tokens, R 64    30.8 (16) / 24.3 (18) / 28.6 (9) / 32.3 (8)
-//   20 layers, 40 heads on 5 of 128, 3200 tokens, R 9             52.1 (32) / 53 (50) / 45.4 (20) / 45.6 (16)
-//   12 layers, 20 heads on 5 of 64, 2048 tokens, R 17             22.5 (16) / 21.1 (18) / 20.7 (9) / 22.8 (8)
-//   8 layers, 32 heads on 8 of 128, 4096 tokens, R 64             41.8 (32) / 40.4 (40) / 41.5 (18) / 47.3 (16)
-//   4 layers, 8 heads on one of 64, 32768 tokens, R 64            35.7 (32) / 32.6 (40) / 36.2 (18) / 37.9 (16)
+// K shared: where the longest runs make fewer than 256 workgroups, the length is the one with the least estimate of the
+// launch, the longest chain a workgroup walks times what the other workgroups of its CU make of it, in tiles of the fast
+// pass at head_dim 128 (0.5 us where a CU holds one workgroup):
+//   chain   3 to open a run (query rows, first tile), each tile of the fast pass, and where a run reaches the causal
+//           diagonal 4 for the second pass and each tile of the general pass;
+//   load    two workgroups on a CU hide little of each other's time where all four wavefronts have rows, more where two
+//           have, nearly all where the whole run takes the general pass (an odd number of row blocks); three fit at head_dim 64;
+//   runs    the combine kernel reads the statistics of every run.
+// The last runs carry the diagonal, so a length whose last run is shorter than the others is often the better one.  Fitted
+// to all lengths from 4 to 64 of 546 launches (sizes drawn over the range of a context switch, keys in the cache and read
+// from memory): on average 1.5 % over the fastest length, 10 % under halving, 8 % under the second rule below.  Measured,
+// us per call on the GPU (halving until 256 workgroups exist / runs for 512 workgroups, or 256 below 20 tiles / this rule;
+// tiles of a run):
+//   18 layers, 8 heads on one kv head of 256, 4096 tokens, R 23   35.7 (16) / 31.6 (10) / 30.1 (19)
+//   4 layers, 16 heads on 4 kv heads of 128, 8192 tokens, R 64    30.6 (16) / 28.3 (17) / 25.6 (18)
+//   28 layers, 28 heads on 4 of 128, 2048 tokens, R 32            49.2 (16) / 57.7 (33) / 46.6 (16)
+//   6 layers, 71 heads on one of 64, 4096 tokens, R 32            44.7 (16) / 55.1 (33) / 39.7 (15)
+//   14 layers, 10 heads on 2 of 128, 8192 tokens, R 32            43.0 (16) / 50.6 (29) / 39.8 (15)
+//   24 layers, 32 heads on 8 of 64, 1024 tokens, R 16             29.8 (16) / 30.6 (32) / 24.2 (10)
+//   16 layers, 8 heads on 2 of 128, 512 tokens, R 32              16.6 (4) / 17.6 (9) / 14.0 (5)
+//   6 layers, 16 heads on 2 of 128, 1024 tokens, R 32             18.5 (4) / 18.7 (9) / 17.7 (6)
+//   8 layers, 32 heads on 8 of 128, 4096 tokens, R 64             44.3 (32) / 41.7 (33) / 38.9 (35)
+//   4 layers, 8 heads on one of 64, 32768 tokens, R 64            36.0 (32) / 33.0 (33) / 30.6 (34)
+//   4 layers, 4 heads on one of 256, 32768 tokens, R 64           36.7 (32) / 42.2 (17) / 38.2 (34)
+//   11 layers, 4 heads on 2 of 128, 2240 tokens, R 43             21.5 (4) / 24.9 (9) / 23.7 (11)
+// The run planes of a shorter length take at most kRunPlaneBytes.  The length goes by n_tokens, not by the valid ones,
+// so that it does not vary from call to call on one workspace.
 // Four runs side by side in a workgroup: halved until 128 workgroups exist, but not below two tiles (us per call, longest
 // runs / 128 / 256 / 512 wanted):
 //   18 layers, one head of 256, 4096 tokens, R 32                 28.0 / 20.8 / 23.7 / 23.7
 //   6 layers, 12 heads of 256, 2048 tokens, R 32                  28.5 / 28.5 / 32.4 / 29.7
+constexpr uint64_t kRunPlaneBytes = 3u << 19;
+static int shared_run_length(const ScoreGeom& g, int head_dim, int64_t columns) {
+    const bool general = g.n_rb % shared_blocks_per_wave(head_dim) != 0;     // no fast pass
+    const float fast_tile = head_dim == 64 ? 0.75f : (head_dim == 128 ? 1.0f : 1.3f);
+    const float general_tile = head_dim == 64 ? 3.0f : (head_dim == 128 ? 3.75f : 2.6f);
+    const int resident = head_dim == 64 ? 3 : 2;                             // workgroups of a CU
+    const float two = general ? 1.1f : (g.rg_per_wg <= 2 ? 1.7f : (head_dim == 64 ? 1.7f : (head_dim == 128 ? 1.8f : 2.4f)));
+    const float load[4] = {0.0f, 1.0f, two, 1.2f * two};
+    const float per_run = 0.13f + 0.02f * static_cast<float>(g.RB);
+    const int first_tail = general ? 0 : (g.N - g.R + 1) / 32, longest = std::min(g.n_tiles, 64);
+    const uint64_t plane = 12ull * g.L * g.Hq * g.rows_p;                    // bytes of one run
+    const int most = static_cast<int>(std::min<uint64_t>(kCombineMaxRuns, kRunPlaneBytes / plane));
+    int best = longest;
+    float least = INFINITY;
+    for (int len = most ? std::max(4, (g.n_tiles + most - 1) / most) : longest; len <= longest; ++len) {
+        const float open = 3.0f;
+        if (open + fast_tile * static_cast<float>(len) > least) break;       // (no longer one costs less)
+        const int runs = (g.n_tiles + len - 1) / len, at = first_tail / len;
+        float chain = first_tail >= len ? fast_tile * static_cast<float>(len) : 0.0f;
+        if (at < runs) {                                                     // the run that reaches the diagonal, and the next
+            const int fast = first_tail - at * len, rest = std::min(len, g.n_tiles - at * len) - fast;
+            if (rest > 0)
+                chain = std::max(chain, fast_tile * static_cast<float>(fast) + (fast ? 4.0f : 0.0f) + general_tile * static_cast<float>(rest));
+            const int behind = std::min(len, g.n_tiles - (at + 1) * len);
+            if (behind > 0) chain = std::max(chain, general_tile * static_cast<float>(behind));
+        }
+        const int64_t per_cu = (columns * runs + 255) / 256;
+        const float beside = per_cu <= resident ? load[per_cu] : load[resident] * static_cast<float>(per_cu) / static_cast<float>(resident);
+        const float cost = (open + chain) * beside + per_run * static_cast<float>(runs);
+        if (cost <= least) {
+            least = cost;
+            best = len;
+        }
+    }
+    return best;
+}
+
 static void shorten_runs(ScoreGeom* g, int head_dim) {
     const bool shared = g->tile_par == 1;
     const int64_t heads = static_cast<int64_t>(g->L) * g->Hkv * ((g->n_rg + g->rg_per_wg - 1) / g->rg_per_wg);
@@ -462,11 +513,7 @@ static void shorten_runs(ScoreGeom* g, int head_dim) {
     if (!shared) {
         while (run > 2 && groups() < 128) run /= 2;
     } else if (groups() < 256) {
-        auto tiles_of = [&](int64_t runs) { return static_cast<int>((g->n_tiles + runs - 1) / runs); };
-        run = tiles_of(512 / heads);
-        if (head_dim != 256 && run < 20) run = tiles_of(256 / heads);
-        run = std::min(std::max(run, 8), 64);
-        if (run < 64 && !(run & (run - 1))) ++run;
+        run = shared_run_length(*g, head_dim, heads);
     }
     if (run >= g->n_tiles) return;
     g->run_len = run;
@@ -499,8 +546,8 @@ static uint64_t score_head_lds_bytes(const ScoreGeom& g, int head_dim) {
 
 // The geometry to launch with, given `available` bytes of scratch.  Shorter runs need a little more (three floats
 // per row and run); a workspace that holds the longest runs only - one made for another shape - is served with
-// these, as long as it holds them.  How much more: at most 512 workgroups of a run and up to eight row blocks each (K
-// shared), 3 floats * 512 * 256 rows = 1.5 MiB; or twice 127 of four runs and two row blocks, less.
+// these, as long as it holds them.  How much more: kRunPlaneBytes where K is shared; otherwise the planes of twice 127
+// workgroups of four runs and two row blocks, less.
 constexpr uint64_t kShortRunsExtraBytes = 2u << 20;
 static ScoreGeom fitted_runs(const ScoreGeom& g, int head_dim, uint64_t available) {
     if (score_head_lds_bytes(g, head_dim)) return g;
