@@ -20,6 +20,7 @@
 
 #include "kv_gemm_kernels.hpp"
 #include "kv_internal.h"
+#include "kv_launch_rules.hpp"
 #include "kv_recompute_kernels.hpp"
 
 using namespace kvs;
@@ -76,13 +77,8 @@ struct OwnGemm {
     uint32_t col_tiles, row_tiles;      // (row tiles: tiled only; a streamed workgroup holds all rows)
 };
 
-// Up to 64 rows the weights are streamed: as many splits (at most 8) as keep every workgroup resident at once, 512 of a
-// row block (two per CU) or 256 of two: for a Llama-2-7B layer q | k | v 5 and 2, o and down 8 and 8, gate | up 2 and 1.
-// A few workgroups more than that are a second round, in which the chip is nearly empty: with 640 wanted (q | k | v
-// 576, gate | up 516) the layer took 122.5 us at 16 rows and 138.6 at 32, with 512 115.6 and 132.4; 384: 117.5 and
-// 133.8; d_model 2048, d_ff 5632, 16 rows 69.9 / 66.9 (384: 67.1); d_model 3072, d_ff 8192 90.0 / 85.8 (87.5); up to 16
-// splits of o and down 119.2.  Undivided gate | up with the activation in its epilogue saves a launch, but one
-// workgroup per CU streams only half as fast as two (d_ff 11008 117.3 us, 8192 114 instead of 104).
+// Up to 64 rows the weights are streamed: one row block with stream_splits, two with as many splits (at most 8) as keep
+// one workgroup on a CU: for a Llama-2-7B layer q | k | v 2 and 2, o and down 8 and 8, gate | up 1 and 1.
 // Above, the row blocks per workgroup (3..8) and the splits that minimise
 //     rounds of 256 workgroups * steps * (0.184 + 0.0453 * row blocks) us
 //     + writing and reading the partial products at 3.25 TB/s each;
@@ -112,8 +108,8 @@ OwnGemm own_gemm_plan(int64_t M, const int64_t* N, int n_mats, int64_t K, uint64
         best.stream = true;
         best.mb = M <= 32 ? 1 : 2;
         best.col_tiles = static_cast<uint32_t>(tiles(kStreamCols));
-        int64_t s = (best.mb == 1 ? 512 : 256) / best.col_tiles;
-        s = std::max<int64_t>(1, std::min<int64_t>({s, 8, room_splits, steps / 16}));
+        int64_t s = std::max<int64_t>(1, std::min<int64_t>({256 / best.col_tiles, 8, room_splits, steps / 16}));
+        if (best.mb == 1) s = stream_splits(best.col_tiles, steps, room_splits);
         best.steps = static_cast<int>((steps + s - 1) / s);
         best.splits = static_cast<int>((steps + best.steps - 1) / best.steps);
         return best;
