@@ -34,4 +34,30 @@ inline int64_t stream_splits(int64_t col_tiles, int64_t steps, int64_t most) {
     return best;
 }
 
+// Recompute attention: one or two (row block, query head) pairs per kv head go to the kernel whose wavefronts share a pair:
+// a layer of 32 rows 93.2 -> 92.1 us (32 heads, d_model 4096, d_ff 512, cache from memory), 64 rows 106.1 -> 104.2; two
+// query heads on each of 16 kv heads, 16 rows 73.4 -> 71.7, 32 rows 85.1 -> 83.4; on each of 8 over 32768 tokens, 32 rows
+// 101.7 -> 82.8.  With three pairs reading the keys three times costs more than the idle wavefront (32 heads, 96 rows 114.7 -> 120.2).
+inline bool few_pairs(int64_t pairs) { return pairs <= 2; }
+
+// With few recomputed rows the attention kernel has too few workgroups to fill 256 CUs: the key ranges are then
+// divided (at least four key tiles per share over the whole cache), as far as there is room for the shares (`most`), until
+// some 512 workgroups exist (two per CU; 768 cost more in partial results than they gain: 512 rows, 32 heads, 356
+// against 344 us per layer).  More than eight shares only where eight do not make 256 workgroups: 128 rows, 32 heads
+// 182 us with 8, 188 with 16, 190 with 4; 4 kv heads, 16 rows 52 us with 16, 53 with 8.
+// Where the wavefronts of a workgroup share a pair, 256 workgroups do (512: the same at one pair, 3 us more at two), of at
+// least eight tiles, or four until 128 exist (8 heads over 1024 tokens, 32 rows: 49.5 us of four tiles, 50.2 of eight; 32
+// heads over 768 80.4 and 79.7).  Up to 640 tokens dividing costs more than it gains, a launch that merges the shares: 512
+// tokens, 16 heads, 16 rows 51.2 us undivided, 53.4 divided in two, 52.9 in the other kernel; two heads on each of 4 kv
+// heads 42.0, 43.8, 41.9; 640 tokens, 32 heads of 64 on 16, 32 rows 50.5, 52.9, 53.7.  At 768 they are even.
+inline int64_t attention_shares(int64_t pairs, int64_t n_kv_heads, int64_t tiles, int64_t most, int waves, int max_shares) {
+    const bool few = few_pairs(pairs);
+    const int64_t base = (few ? pairs : (pairs + waves - 1) / waves) * n_kv_heads;
+    int64_t shares = (few ? 256 : 512) / base;
+    if (shares > 8) shares = std::max<int64_t>(8, std::min<int64_t>(max_shares, 256 / base));
+    const int64_t in_few = tiles <= 20 ? 1 : std::max<int64_t>(tiles / 8, std::min<int64_t>(tiles / 4, 128 / base));
+    shares = std::min<int64_t>({shares, few ? in_few : tiles / 4, most});
+    return std::max<int64_t>(shares, 1);
+}
+
 }  // namespace kvs

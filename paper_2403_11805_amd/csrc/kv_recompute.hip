@@ -164,26 +164,10 @@ uint64_t attention_share_bytes(const kv_shape_t& s, int64_t M) {
     return static_cast<uint64_t>(M) * s.n_q_heads * (s.head_dim + 2) * 4;
 }
 
-// One or two (row block, query head) pairs per kv head go to the kernel whose wavefronts share a pair: a layer of 32 rows
-// 132.4 -> 129.6 us (32 heads, d_model 4096), 48 rows 137 -> 133.7, 64 rows 145 -> 142.8, 32 heads on 16 kv heads, 32 rows
-// 114.5 -> 107.8.  With three pairs reading the keys three times costs more than the idle wavefront (80 rows 153 -> 159).
-bool few_pairs(int64_t pairs) { return pairs <= 2; }
-
-// With few recomputed rows the attention kernel has too few workgroups to fill 256 CUs: the key ranges are then
-// divided (at least four key tiles per share over the whole cache), as far as there is room for the shares, until
-// some 512 workgroups exist (two per CU; 768 cost more in partial results than they gain: 512 rows, 32 heads, 356
-// against 344 us per layer).  More than eight shares only where eight do not make 256 workgroups: 128 rows, 32 heads
-// 182 us with 8, 188 with 16, 190 with 4; 4 kv heads, 16 rows 52 us with 16, 53 with 8.  Where the wavefronts of a
-// workgroup share a pair, 256 workgroups of at least eight tiles do (512: the same at one pair, 3 us more at two).
 int attention_splits(const kv_shape_t& s, int64_t M, uint64_t room) {
     const int64_t pairs = static_cast<int64_t>(s.n_q_heads / s.n_kv_heads) * ((M + 31) / 32);
-    const bool few = few_pairs(pairs);
-    const int64_t base = (few ? pairs : (pairs + kAttnWaves - 1) / kAttnWaves) * s.n_kv_heads;
-    int64_t splits = (few ? 256 : 512) / base;
-    if (splits > 8) splits = std::max<int64_t>(8, std::min<int64_t>(kMaxSplits, 256 / base));
-    splits = std::min<int64_t>(splits, (s.n_tokens + 31) / 32 / (few ? 8 : 4));
-    splits = std::min<int64_t>(splits, static_cast<int64_t>(room / attention_share_bytes(s, M)));
-    return static_cast<int>(std::max<int64_t>(splits, 1));
+    return static_cast<int>(attention_shares(pairs, s.n_kv_heads, (s.n_tokens + 31) / 32,
+                                             static_cast<int64_t>(room / attention_share_bytes(s, M)), kAttnWaves, kMaxSplits));
 }
 
 // Shares that the workspace has a place of their own for.  Part of what kv_recompute_workspace_bytes has always

@@ -82,9 +82,13 @@ def test_nothing_behind_the_last_token_is_used(Hkv, Hq, D, N, T, missing):
 @pytest.mark.parametrize("Hkv,Hq,D,N,T,missing", [
     (1, 1, 64, 64, 8, [2]),                      # one pair of 8 rows, one tile: three wavefronts have none
     (1, 1, 128, 96, 8, [0, 3, 11]),              # one pair of 24 rows, three tiles, undivided
-    (1, 1, 128, 1024, 16, [63]),                 # one pair, divided in four: eight tiles a share, two a wavefront
-    (16, 16, 64, 512, 8, [10]),                  # divided, kv heads dealt to the XCDs; the row sees less than a share
-    (2, 2, 128, 1184, 16, [1, 30, 73]),          # two pairs: 32 rows and 16; 37 tiles, shares of 10, the last one short
+    (1, 1, 128, 1024, 16, [63]),                 # one pair, divided in eight: four tiles a share, one a wavefront
+    (16, 16, 64, 512, 8, [10]),                  # 16 tiles, undivided, kv heads dealt to the XCDs
+    (16, 16, 64, 1024, 8, [10]),                 # divided, kv heads dealt to the XCDs; the row sees less than a share
+    (32, 32, 64, 1024, 16, [3, 62]),             # divided in four: eight tiles a share, two a wavefront
+    (2, 2, 128, 640, 16, [0, 39]),               # 20 tiles, the most that are not divided: five a wavefront
+    (2, 2, 128, 672, 16, [0, 41]),               # 21 tiles, divided in five, the last share of one
+    (2, 2, 128, 1184, 16, [1, 30, 73]),          # two pairs: 32 rows and 16; 37 tiles, shares of five, the last of two
     (8, 16, 128, 224, 8, [0, 27]),               # two heads on a kv head, undivided, rows at both ends
     (3, 3, 64, 2048, 16, [5, 64, 100, 127]),     # two pairs of 32 rows, kv heads in plain order
 ])

@@ -21,6 +21,8 @@ def rules(tmp_path_factory):
     handle = ctypes.CDLL(lib)
     handle.stream_splits.restype = ctypes.c_int64
     handle.stream_splits.argtypes = [ctypes.c_int64] * 3
+    handle.attention_shares.restype = ctypes.c_int64
+    handle.attention_shares.argtypes = [ctypes.c_int64] * 4
     return handle
 
 
@@ -52,3 +54,22 @@ def test_splits_of_the_streamed_gemm_stay_in_their_limits(rules):
             for most in (0, 1, 2, 3, 8, 16):
                 s = rules.stream_splits(tiles, steps, most)
                 assert 1 <= s <= max(1, min(8, most, steps // 16))
+
+
+@pytest.mark.parametrize("pairs,kv_heads,tokens,good", [
+    (1, 16, 512, (1,)),            # 51.2 us undivided, 53.4 in two shares
+    (2, 16, 512, (1,)),            # 63.7, 65.3
+    (2, 4, 512, (1,)),             # 42.0, 43.9
+    (2, 16, 640, (1,)),            # 50.5, 52.9
+    (1, 8, 1024, (8,)),            # 49.5 in eight, 50.2 in four, 52.8 undivided
+    (2, 16, 1024, (4,)),           # 66.2 in four, 66.5 in eight, 67.5 undivided
+    (1, 32, 4096, (8,)),
+    (2, 32, 4096, (4,)),
+    (2, 1, 4096, (16,)),
+    (3, 32, 4096, (8,)),           # a wavefront per pair
+    (64, 32, 4096, (1,)),
+])
+def test_shares_of_the_attention(rules, pairs, kv_heads, tokens, good):
+    assert rules.attention_shares(pairs, kv_heads, tokens // 32, 100) in good
+    assert rules.attention_shares(pairs, kv_heads, tokens // 32, 3) <= 3
+    assert rules.attention_shares(pairs, kv_heads, tokens // 32, 0) == 1
