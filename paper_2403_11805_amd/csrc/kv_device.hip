@@ -649,6 +649,10 @@ int32_t kv_score_chunks_static(const kv_shape_t* shape, const void* q, int32_t n
 //   32 layers, 32 on 8 of 128, 16384 tokens, R 32 315 / 295;  24 layers, 32 on 4 of 128, 16384, R 30 183 / 173
 //   22 layers, 48 on 12 of 128, 8288, R 3 164 / 158;  32 layers, 32 on 8 of 64, 16384, R 64 308 / 299
 //   below, the next call finds K in the cache: 4 layers of 16384 tokens (128 MiB) 59 / 63
+// The size is the allocated planes', also where only a part is valid: the partials that are filled in for the padding take
+// the cache all the same.  32 on 8 of 128, R 64, 8 layers of 32768 tokens, 8192 valid (128 MiB read) 147 / 142, 16384
+// 154 / 152; 8 layers, 16 on 4 of 256, 16384 tokens, 4096 valid (64 MiB) 81 / 61; 32 layers of 32768, 4096 valid 600 / 608.
+// Only the fast pass reads past the caches, so the rule asks for it: row blocks that fill every wavefront's.
 constexpr uint64_t kReadOnceBytes = 256u << 20;
 static int32_t score_launch(const kv_shape_t* shape, const ScoreGeom& g, int nrbw, const void* q, const void* kv,
                             void* workspace, float* chunk_mass, float* density, void* stream) {
@@ -663,7 +667,8 @@ static int32_t score_launch(const kv_shape_t* shape, const ScoreGeom& g, int nrb
                     (g.n_rg + g.rg_per_wg - 1) / g.rg_per_wg, g.L * g.Hkv);
     const _Float16* qp = static_cast<const _Float16*>(q);
     const _Float16* kp = static_cast<const _Float16*>(kv);
-    const bool once = grid.y == 1 && static_cast<uint64_t>(g.L) * g.Hkv * g.N * shape->head_dim * 2u >= kReadOnceBytes;
+    const bool once = grid.y == 1 && g.n_rb % shared_blocks_per_wave(shape->head_dim) == 0 &&
+                      static_cast<uint64_t>(g.L) * g.Hkv * g.N * shape->head_dim * 2u >= kReadOnceBytes;
 #define KV_SCORE_SHARED_T(DD, SBT)                                                                    \
     do {                                                                                             \
         if (once) hipLaunchKernelGGL((score_tiles_shared_kernel<DD, SBT, true>), grid, dim3(256), 0, st, qp, kp, g, ws); \

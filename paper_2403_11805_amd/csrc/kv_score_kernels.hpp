@@ -331,7 +331,7 @@ __global__ __launch_bounds__(256) void score_tiles_kernel(const _Float16* __rest
 //    range there (workgroup-wide decision), or instead of the fast pass if the row
 //    blocks of a kv head do not fill every wavefront's two.
 //
-// ONCE: K is read past the caches (the host's rule).
+// ONCE: the fast pass reads K past the caches (the host's rule).
 //
 // Row blocks per wavefront: two, but one at head_dim 256, where the two query blocks alone would hold 128
 // registers: 171 spilled, and 4.4 us went by per tile of 32 tokens (18 layers x 8 heads x 4096 tokens, the same

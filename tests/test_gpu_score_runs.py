@@ -194,11 +194,25 @@ def test_runs_of_any_length(geom, R, n_valid):
     check(score_with(ks, q, kv, n_valid, kvs.kv_score_workspace_bytes(ks, R)), want)
 
 
-@pytest.mark.parametrize("L,D,T", [(4, 64, 8), (4, 64, 16), (2, 128, 16), (2, 128, 32)])
-def test_keys_read_past_the_caches(L, D, T):
+def exact_masses(q, k, T):
+    """Chunk masses of query rows q [heads][R][D] (the newest tokens) over keys k [N][D] in 64 bits, columns averaged over
+    the rows that see them."""
+    R, N = q.shape[1], k.shape[0]
+    s = q.double() @ k.double().T / q.shape[2] ** 0.5
+    seen = torch.arange(N, device=DEV) <= torch.arange(N - R, N, device=DEV)[:, None]
+    a = torch.softmax(s.masked_fill(~seen, float("-inf")), -1).sum(1) / seen.sum(0)
+    return a.view(q.shape[0], N // T, T).sum(-1)
+
+
+@pytest.mark.parametrize("L,D,N,T", [(4, 64, 65536, 8), (4, 64, 65536, 16), (4, 64, 65536, 32), (2, 128, 65536, 8),
+                                     (2, 128, 65536, 16), (2, 128, 65536, 32), (2, 256, 32768, 8), (2, 256, 32768, 16),
+                                     (2, 256, 32768, 32)])
+def test_keys_read_past_the_caches(L, D, N, T):
     """256 MiB of keys, the least that is read past the caches, against a call per layer, which reads its share through
-    them: the same runs (256 workgroups of the longest in a layer), the same sums, the same bits."""
-    Hkv, Hq, N, R = 8, 24, 65536, 5
+    them: the same runs (256 workgroups of the longest in all, and a workspace for the longest in a layer), the same sums,
+    the same bits; and some heads against 64 bits.  Four row blocks per kv head, so that the fast pass, which alone reads
+    past the caches, takes every tile below the diagonal."""
+    Hkv, Hq, R = 8, 32, 5
     gen = torch.Generator(device=DEV)
     gen.manual_seed(73)
     kv = torch.empty((L, 2, Hkv, N, D), dtype=torch.float16, device=DEV)
@@ -211,7 +225,8 @@ def test_keys_read_past_the_caches(L, D, T):
         ks = kvs.Shape(layers, Hkv, Hq, D, N, T, 64)
         cm = torch.full((layers, Hq, ks.n_chunks), float("nan"), dtype=torch.float32, device=DEV)
         d = torch.zeros(ks.n_chunks, dtype=torch.float32, device=DEV)
-        ws = torch.full((kvs.kv_score_workspace_bytes(ks, R),), 0xff, dtype=torch.uint8, device=DEV)
+        ws = torch.full((longest_runs_bytes(synth.Geometry(layers, Hkv, Hq, D, N, T, 64), R, 64),), 0xff, dtype=torch.uint8,
+                        device=DEV)
         kvs.kv_score_chunks(ks, qs, kvs_, oracle.NORM_VISIBLE, ws, cm, d)
         torch.cuda.synchronize()
         return cm
@@ -220,3 +235,7 @@ def test_keys_read_past_the_caches(L, D, T):
     assert torch.isfinite(together).all()
     for l in range(L):
         assert torch.equal(together[l], masses(1, q[l:l + 1].contiguous(), kv[l:l + 1].contiguous())[0])
+    for l, kvh in ((0, 0), (L - 1, Hkv - 1)):
+        heads = slice(kvh * 4, kvh * 4 + 4)
+        np.testing.assert_allclose(together[l, heads].cpu().numpy(), exact_masses(q[l, heads], kv[l, 0, kvh], T).cpu().numpy(),
+                                   rtol=1e-4, atol=1e-30)
