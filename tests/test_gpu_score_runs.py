@@ -11,6 +11,7 @@ import paper_2403_11805_amd as kvs
 from paper_2403_11805_amd import synth
 
 from gpu_util import DEV, both_shapes, gpu_score
+from test_score_run_rule import runs_of
 
 pytestmark = pytest.mark.gpu
 
@@ -28,6 +29,16 @@ def check(got, want):
     for g, w in zip(got, want):
         assert np.all(np.isfinite(g))
         np.testing.assert_allclose(g, w, rtol=1e-4, atol=1e-30)
+
+
+def exact_masses(q, k, T):
+    """Chunk masses of query rows q [heads][R][D] (the newest tokens) over keys k [N][D] in 64 bits, columns averaged over
+    the rows that see them."""
+    R, N = q.shape[1], k.shape[0]
+    s = q.double() @ k.double().T / q.shape[2] ** 0.5
+    seen = torch.arange(N, device=DEV) <= torch.arange(N - R, N, device=DEV)[:, None]
+    a = torch.softmax(s.masked_fill(~seen, float("-inf")), -1).sum(1) / seen.sum(0)
+    return a.view(q.shape[0], N // T, T).sum(-1)
 
 
 @pytest.mark.parametrize("geom,R,n_valid", [
@@ -178,30 +189,42 @@ def test_many_runs_and_row_blocks(R):
           oracle.score_chunks(os_, q.numpy(), kv.numpy(), oracle.NORM_VISIBLE))
 
 
+@pytest.mark.parametrize("R,N,more_than", [(16, 1060864, 512), (64, 532480, 256), (96, 270336, 128), (160, 270336, 128)])
+def test_more_runs_than_one_pass_of_the_combine_kernel(R, N, more_than):
+    """The combine kernel collects the runs' bits `more_than` at a time, for one, two and three to eight row blocks per
+    head: a key far above its run's reference in the first runs and in the last, met by the rows of one block only."""
+    g = synth.Geometry(1, 1, 4, 64, N, 16, 64)
+    ks, _ = both_shapes(g)
+    assert runs_of(*g[:6], R) > more_than
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(59)
+    kv = (torch.randn(ks.kv_dims, generator=gen, device=DEV) * 0.5).half()
+    kv[0, 0, 0, 20007] = 20.0
+    kv[0, 0, 0, N - 1000] = 20.0
+    q = (torch.randn((1, 4, R, 64), generator=gen, device=DEV) * 6).half()
+    q -= q.float().mean(-1, keepdim=True).half()                  # hardly anything to the hot keys
+    q[0, 1, max(R - 32, 0):] = 2.0
+    cm, d = gpu_score(ks, q, kv, oracle.NORM_VISIBLE)
+    want = exact_masses(q[0], kv[0, 0, 0], 16)
+    check((cm[0], d), (want.cpu().numpy(), (want.mean(0) / 16).cpu().numpy()))
+
+
 @pytest.mark.parametrize("geom,R,n_valid", [
     ((18, 1, 8, 256, 1600, 16, 64), 23, 1589),   # 36 workgroups a run: seven runs of eight tiles, the last of two
     ((20, 5, 20, 128, 1600, 32, 64), 9, 1600),   # 100: five runs of ten tiles
     ((4, 4, 16, 128, 4096, 8, 64), 40, 4075),    # 16: runs of nine tiles, 128 tiles, the last of two
     ((1, 1, 6, 64, 2080, 16, 64), 32, 2017),     # one workgroup a run: runs of four tiles, 65 tiles, the last of one is padding
+    ((10, 1, 8, 256, 2464, 16, 64), 23, 2300),   # 20: runs of nine tiles at head_dim 256, 77 tiles, the last of five is padding
+    ((18, 1, 8, 256, 2272, 16, 64), 23, 2250),   # 36: seven runs of eleven tiles, the last of five
 ])
 def test_runs_of_any_length(geom, R, n_valid):
-    """Runs whose length is no power of two: the combine kernel finds a tile's run by a product with 1 / length."""
+    """Runs of other lengths too than powers of two: the combine kernel finds a tile's run by a product with 1 / length."""
     ks, os_ = both_shapes(synth.Geometry(*geom))
     kv = synth.make_kv(synth.Geometry(*geom), 71, "cpu", 1, 4.0)
     q = (synth.make_q(synth.Geometry(*geom), 71, R).float() * 6).to(torch.float16)
     want = oracle.score_chunks_valid(os_, q.numpy(), kv.numpy(), n_valid, oracle.NORM_VISIBLE)
     kv[:, :, :, n_valid:] = float("nan")
     check(score_with(ks, q, kv, n_valid, kvs.kv_score_workspace_bytes(ks, R)), want)
-
-
-def exact_masses(q, k, T):
-    """Chunk masses of query rows q [heads][R][D] (the newest tokens) over keys k [N][D] in 64 bits, columns averaged over
-    the rows that see them."""
-    R, N = q.shape[1], k.shape[0]
-    s = q.double() @ k.double().T / q.shape[2] ** 0.5
-    seen = torch.arange(N, device=DEV) <= torch.arange(N - R, N, device=DEV)[:, None]
-    a = torch.softmax(s.masked_fill(~seen, float("-inf")), -1).sum(1) / seen.sum(0)
-    return a.view(q.shape[0], N // T, T).sum(-1)
 
 
 @pytest.mark.parametrize("L,D,N,T", [(4, 64, 65536, 8), (4, 64, 65536, 16), (4, 64, 65536, 32), (2, 128, 65536, 8),
