@@ -109,8 +109,9 @@ __device__ __forceinline__ void gemm_store8(const GemmArgs& g, int mat, int spli
 // the scheduling barriers keep the compiler from pulling the operand permutes of later steps, and with them the
 // waits for their loads, in front.  Weights are read once and marked non-temporal (8 % of a loop over the four
 // launches of a layer).
-// Measured in a kernel trace, the four launches of a Llama-2-7B layer (404 MB of weights) at 16 rows: 82 us (4.9 TB/s;
-// 86 with the last few workgroups in a second round, the LDS-tiled kernel before it 107).
+// Measured in a kernel trace, the four launches of a Llama-2-7B layer (404 MB of weights) at 16 rows: 80 us (5.05 TB/s;
+// 82 with two workgroups on a third of the CUs in gate | up, 86 with the last few in a second round, the LDS-tiled kernel
+// before it 107).
 // Grid (column tiles of all matrices, splits), 256 threads; at most MB * 32 rows.
 template <int MB>
 __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(GemmArgs g) {

@@ -356,7 +356,7 @@ __device__ __forceinline__ void attention_tile(const ru4_t* ktile, const _Float1
 constexpr int kAttnWaves = 4;
 constexpr int kMaxSplits = 16;     // workgroups that may share the key range of a row block
 // Measured, 32 heads of 128 over 4096 tokens (kernel alone): 2048 rows anywhere in the cache 123 us, 304 rows 45 us,
-// 16 rows 7.8 to 13 by where they lie (at token 2928 13.1; 12.4 in recompute_attention_few_kernel, which takes them).  Eight
+// 16 rows 7.8 to 13.5 by where they lie (at token 2928 13.5; 12.6 in recompute_attention_few_kernel, which takes them).  Eight
 // wavefronts per workgroup, loads behind branches - the compiler then waits for every load in flight before it parks a
 // tile, so that the second tile ahead never is -, accumulators in AGPRs and rescaled whenever a maximum moved: 160, 57 and
 // 13.5 us.  The unequal key ranges of a causal mask leave the chip waiting
@@ -532,8 +532,10 @@ __global__ __launch_bounds__(64 * kAttnWaves, 2) void recompute_attention_kernel
 // The same with few (row block, query head) pairs per kv head, where most wavefronts of the kernel above would have no
 // pair of their own: the four wavefronts of a workgroup share ONE pair and take the key tiles of the workgroup's share in
 // turn, each through a tile of LDS of its own and with no barrier before their outputs meet at the end.  A tile of a lone
-// wavefront is a serial chain of LDS reads, MFMAs and exponentials, some 3000 cycles; four chains side by side make
-// 16 rows 0.7 us shorter (13.1 -> 12.4) and take 3 us off a layer of 32 rows (the rule: few_pairs).
+// wavefront is a serial chain of LDS reads, MFMAs and exponentials, some 3000 cycles, and four chains run side by side.  The
+// kernel alone in a trace, 32 heads of 128 over 4096 tokens, the other kernel / this one: 16 rows 13.5 / 12.6 us (48 MB of
+// keys and values at 3.8 TB/s), 32 rows 14.9 / 13.4, 48 rows 16.0 / 15.9, 64 rows 19.0 / 18.7; longer contexts gain more (the rule and
+// layers: few_pairs).
 // Grid (pairs, kv heads, shares).
 template <int D, bool SPLIT>
 __global__ __launch_bounds__(64 * kAttnWaves, 2) void recompute_attention_few_kernel(
